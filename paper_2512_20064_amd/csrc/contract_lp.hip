@@ -25,14 +25,22 @@
 // Complex arithmetic uses the real embedding of the site tensor: real column
 // (c, p) of branch i multiplies the interleaved left vector (re, im) by
 // (Re a, -Im a) for p = 0 (real part of W) and (Im a, Re a) for p = 1
-// (imaginary part).  pack_kernel writes that embedding once per site,
-// transposed so that K is contiguous ("NT" operands: both MFMA operands are
-// 16-byte runs of K) and K-blocked (see kblk_off), each branch padded with
-// zero columns to a multiple of 128 complex columns and K padded with zeros
-// to a multiple of 64.  The
-// embedding does exactly the algorithmic 8 real flops per complex
-// multiply-add; its cost is that the site-tensor operand is twice as large
-// as the complex data, which only matters for L2/LDS traffic.
+// (imaginary part).  Only the p = 0 rows are stored: pack_kernel writes one
+// row per complex column, transposed so that K is contiguous ("NT" operands:
+// both MFMA operands are 16-byte runs of K) and K-blocked (see kblk_off),
+// each branch padded with zero columns to a multiple of the tile and K padded
+// with zeros to a multiple of 64.  The p = 1 operand is the p = 0 one with
+// every (re, im) pair of K values swapped and the new first member negated,
+// which a lane does to its own registers (the turn functions below): exact,
+// since fp16, bf16, E4M3 and E2M3 rounding are symmetric in sign.  The
+// products do exactly the algorithmic 8 real flops per complex multiply-add.
+//
+// What bounds the plateau launches (65536 x 1024 x 4096 complex): the matrix
+// cores at the clock the power limit leaves, then LDS: per slice a wave reads
+// 64 rows and 64 columns of each plane.  With both rows of the embedding
+// stored (half as much again read from LDS and L2, twice the packing) fp16f6
+// took 3.55 ms per launch and bf16x3 4.95; now 3.1 and 4.5 (chi = 1024 chains,
+// whole sweep: 48.5 -> 42.7 ms and 14.9 -> 13.9 ms).
 
 #include "e2m3.h"
 #include "sweep.h"
@@ -91,21 +99,20 @@ __global__ __launch_bounds__(256) void pack_kernel(const PackProb* probs, const 
                                             : make_float2(0.f, 0.f);
   }
   __syncthreads();
-  // 128 output rows (64 columns x 2 parts) of 64 real K each, written as
-  // 8 chunks of 8 elements.
+  // 64 output rows (the p = 0 row of every column) of 64 real K each, written
+  // as 8 chunks of 8 elements.
   T* Bh = (T*)a.Bh;
   T* Bl = (T*)a.Bl;
 #pragma unroll
-  for (int it = 0; it < 2 * PK_C * 8 / 256; ++it) {
+  for (int it = 0; it < PK_C * 8 / 256; ++it) {
     const int idx = it * 256 + tid;
-    const int rowl = idx >> 3, ch = idx & 7;
-    const int c = rowl >> 1, p = rowl & 1;
+    const int c = idx >> 3, ch = idx & 7;
     float v[8];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const float2 z = tile[ch * 4 + m][c];
-      v[2 * m] = p ? z.y : z.x;
-      v[2 * m + 1] = p ? z.x : -z.y;
+      v[m] = z.x;
+      v[4 + m] = -z.y;
     }
     typename Vec8<T>::type h, lo;
 #pragma unroll
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const PackProb* probs, const 
       h[e] = (T)v[e];
       lo[e] = (T)(v[e] - (float)h[e]);
     }
-    const size_t orow = ((size_t)br * a.CP + c0 + c) * 2 + p;
+    const size_t orow = (size_t)br * a.CP + c0 + c;
     const size_t off = kblk_off(orow, 2 * l0 + ch * 8, a.Kp);
     *reinterpret_cast<typename Vec8<T>::type*>(Bh + off) = h;
     if (NPROD == 3) *reinterpret_cast<typename Vec8<T>::type*>(Bl + off) = lo;
@@ -127,16 +134,33 @@ constexpr int BK = kLpBK;            // real K per pipeline stage
 constexpr int ARR = BM * BK * 2;     // bytes of one left-vector tile in a stage (8 KiB)
 static_assert(BM == 256 && BK == 16, "layout below assumes 256-row tiles and 16-K stages");
 
-// Tile variants (sweep.h): NWC wave columns of 64 rows x 128 real columns
-// each, over 4 wave rows.  Wide: NWC = 2, a 256 x 256 real tile of 8 waves;
-// narrow: NWC = 1, 256 x 128 real, 4 waves.  Every wave runs the same code on
-// the same 64 x 128 block shape, so both variants give the same bits.
+// Tile variants (sweep.h): NWC wave columns of 64 rows x 64 complex columns
+// each, over 4 wave rows.  Wide: NWC = 2, a 256 x 128 complex tile of 8 waves;
+// narrow: NWC = 1, 256 x 64, 4 waves.  Every wave runs the same code on the
+// same 64 x 64 block shape, so both variants give the same bits.
 template <int NWC>
 struct LpTile {
-  static constexpr int BN = 128 * NWC;            // real columns (packed rows) per workgroup
+  static constexpr int BN = 64 * NWC;             // complex columns (packed rows) per workgroup
   static constexpr int NTHR = 256 * NWC;          // 4 x NWC waves
   static constexpr int BARR = BN * BK * 2;        // bytes of one site-tensor tile in a stage
 };
+
+// A wave's 64 complex columns as MFMA blocks: acc[rb][2 b] and acc[rb][2 b + 1]
+// hold the real and imaginary parts of the 32 columns of block b, lane j the
+// column wave_col(b, j).  This order keeps the partial weights' additions
+// those of 16-column blocks taken in order (store_partials).
+__device__ inline int wave_col(int b, int j) { return (j >> 4) * 32 + b * 16 + (j & 15); }
+
+// The p = 1 row of the embedding from the p = 0 row, per lane: (x, y) ->
+// (-y, x).  With the real parts of 4 complex in one half of a lane's 8 K
+// values and the imaginary ones in the other (kblk_off) that is an exchange
+// of the halves and two sign flips.
+template <typename V8>
+__device__ inline V8 turn(V8 v) {
+  typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+  const uintx4 w = __builtin_bit_cast(uintx4, v);
+  return __builtin_bit_cast(V8, uintx4{w[2] ^ 0x80008000u, w[3] ^ 0x80008000u, w[0], w[1]});
+}
 
 // LDS rows are 32 bytes (16 K values = 2 chunks of 16 bytes).  The chunk is
 // XOR-swizzled by row bits 2 and 3 so that the 16-byte reads of 8 or 16
@@ -149,7 +173,7 @@ __device__ inline int lds_off(int row, int chunk) { return row * 32 + ((chunk ^ 
 // is not waited on.
 constexpr unsigned vmcnt_lgkm0_imm(unsigned n) { return (n & 0xF) | (0x7u << 4); }
 
-// Load instruction idx (0 .. groups-1) of a stage: one KiB = 32 rows of one
+// Load instruction idx (0 .. groups-1) of a slice: one KiB = 32 rows of one
 // operand tile.  The NL left-vector tiles come first (8 row groups each),
 // then the NB site-tensor tiles (BN/32 row groups each).
 template <int NWC>
@@ -168,10 +192,36 @@ __device__ inline void load_slot(int idx, int NL, int& q, int& rg, int& ldst) {
 }
 
 // Partial branch weights of the tile, one per wave column (fixed
-// granularity: 64 complex columns = the 4 column blocks of a wave), summed
-// per lane over the blocks in order, across the 32 lanes of a half by an xor
-// butterfly, staged in LDS and stored as one run of partials per row.  The
-// order of every addition is the same in both variants.
+// granularity: the 64 complex columns of a wave), staged in LDS and stored as
+// one run of partials per row.  Per row and part (re, im) the sum runs over
+// the columns 16 + t, t, 32 + t, 48 + t (fused multiply-adds in that order),
+// then over t by an xor butterfly (8, 4, 2, 1), then re + im: the same order
+// in both variants.
+// Lane j of a 32-lane half holds columns t and 16 + t (j = t < 16) or 32 + t
+// and 48 + t (j = 16 + t), both parts; swapping 16-lane rows between the two
+// parts gives every lane one part's four columns (lanes t the real parts,
+// 16 + t the imaginary ones), and after a rotate-add by 8 the values repeat
+// with period 8, so that rotations by 4, 2 and 1 meet the butterfly's
+// partners.  Registers and DPP only: no LDS permutes.
+template <int R>
+__device__ inline float add_ror(float s) {
+  return s + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x120 + R, 0xF, 0xF, true));
+}
+__device__ inline float part_sum(float re0, float im0, float re1, float im1) {
+  const auto p0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(re0), __float_as_uint(im0), false, false);
+  const auto p1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(re1), __float_as_uint(im1), false, false);
+  const float x0 = __uint_as_float(p0[0]), x1 = __uint_as_float(p1[0]);
+  const float x2 = __uint_as_float(p0[1]), x3 = __uint_as_float(p1[1]);
+  float s = __builtin_fmaf(x0, x0, x1 * x1);
+  s = __builtin_fmaf(x2, x2, s);
+  s = __builtin_fmaf(x3, x3, s);
+  s = add_ror<8>(s);
+  s = add_ror<4>(s);
+  s = add_ror<2>(s);
+  s = add_ror<1>(s);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
 template <int NWC>
 __device__ inline void store_partials(const floatx16 (&acc)[2][4], float* red, int wave, int wr, int half, int j,
                                       int tid, int m0, int rows, float* qpart, size_t qrow, int q0) {
@@ -179,11 +229,7 @@ __device__ inline void store_partials(const floatx16 (&acc)[2][4], float* red, i
   for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      float s = 0.f;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) s += acc[rb][cb][v] * acc[rb][cb][v];
-#pragma unroll
-      for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 32);
+      const float s = part_sum(acc[rb][0][v], acc[rb][1][v], acc[rb][2][v], acc[rb][3][v]);
       const int r = wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
       if (j == 0) red[r * NWC + wave % NWC] = s;
     }
@@ -199,27 +245,48 @@ __device__ inline void store_partials(const floatx16 (&acc)[2][4], float* red, i
   }
 }
 
-// W element store: a global-memory (not flat) store marked nontemporal.  W
-// is written once per launch and read back by the measurement only for the
-// chosen branch, long after the 2 GiB of a plateau launch has left the
-// caches, so its lines need not displace operand tiles in L2 (1-4 % per
-// launch, standalone timing of the headline shape).
-__device__ inline void store_w(float* p, float x) {
-  __builtin_nontemporal_store(x, (__attribute__((address_space(1))) float*)p);
+// W element store (one complex): a global-memory (not flat) store marked
+// nontemporal.  W is written once per launch and read back by the measurement
+// only for the chosen branch, long after the 2 GiB of a plateau launch has
+// left the caches, so its lines need not displace operand tiles in L2 (1-4 %
+// per launch, standalone timing of the headline shape).
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+__device__ inline void store_w(float2* p, float re, float im) {
+  __builtin_nontemporal_store(floatx2{re, im}, (__attribute__((address_space(1))) floatx2*)p);
 }
 
-// Pipeline: stage kt lives in LDS buffer kt % NST.  Operand tiles go straight
-// from memory into LDS (global_load_lds_dwordx4: no staging registers and no
-// LDS store phase), NST-1 stages ahead of the stage being read from LDS,
-// which is itself one stage ahead of the MFMAs (see open_stage below).
-// One stage of MFMAs is ~1500 cycles per SIMD.  The wide variant has a
-// 5-stage ring (5 x 32 KiB = the whole 160 KiB for bf16x3, one workgroup
-// per CU); the narrow one a 3-stage ring (3 x 24 KiB), two workgroups per CU.
+// W of a wave's block: output lane (j, half) of a 32x32 MFMA block holds its
+// column's rows 8*(v/4) + 4*half + v%4.  Runs of 16 lanes store 128
+// contiguous bytes of a row.
+__device__ inline void store_w_block(const floatx16 (&acc)[2][4], float2* W, size_t ncols, int m0, int rows,
+                                     size_t col0, int c0, int chi_r, int half, int j) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int cw = wave_col(b, j);
+      if (c0 + cw < chi_r) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int gr = m0 + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+          if (gr < rows) store_w(W + (size_t)gr * ncols + col0 + cw, acc[rb][2 * b][v], acc[rb][2 * b + 1][v]);
+        }
+      }
+    }
+  }
+}
+
+// Pipeline: a stage is two 16-K slices (one barrier per 32 real K) and lives
+// in LDS buffer (stage % NST).  Operand tiles go straight from memory into LDS
+// (buffer loads to LDS: no staging registers and no LDS store phase), up to
+// NST-1 stages ahead of the stage being read.  Ring: wide 144-160 KiB, one
+// workgroup per CU; narrow at most 80 KiB and 256 registers, two workgroups
+// per CU.
+// (The body is a device function template with one plain kernel per variant
+// below.)
 template <typename T, int NPROD, int NWC>
-__global__ __launch_bounds__(LpTile<NWC>::NTHR, 1) void contract_lp_kernel(const ContractLpProb* probs,
-                                                                          const int* tn_start, int nprob,
-                                                                          int tn_total, int tiles_m, int per_xcd,
-                                                                          int group_m, const ChunkArgs* chp) {
+__device__ inline void contract_lp_kernel(const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total,
+                                        int tiles_m, int per_xcd, int group_m, const ChunkArgs* chp) {
   typedef typename Vec8<T>::type V8;
   typedef LpTile<NWC> Tile;
   // Products per complex product: 3 = Lh*Bh + Lh*Bl + Ll*Bh (split form);
@@ -227,14 +294,15 @@ __global__ __launch_bounds__(LpTile<NWC>::NTHR, 1) void contract_lp_kernel(const
   // and the omitted product adds exact zeros); 1 = Lh*Bh.
   constexpr int NL = NPROD >= 2 ? 2 : 1;    // left-vector tiles per stage: Ah, [Al]
   constexpr int NB = NPROD == 3 ? 2 : 1;    // site-tensor tiles per stage: Bh, [Bl]
-  constexpr int NST = NWC == 2 ? 5 : 3;
-  constexpr int STAGE = NL * ARR + NB * Tile::BARR;
-  constexpr int GROUPS = NL * 8 + NB * (Tile::BN / 32);
+  constexpr int SLICE = NL * ARR + NB * Tile::BARR;
+  constexpr int STAGE = 2 * SLICE;
+  constexpr int NST = (NWC == 2 ? 160 : 80) * 1024 / STAGE;
+  constexpr int GROUPS = NL * 8 + NB * (Tile::BN / 32);  // 1 KiB load instructions per slice
   constexpr int NWAVE = 4 * NWC;
-  static_assert(GROUPS % NWAVE == 0, "loads must divide evenly over the waves");
-  constexpr int IPW = GROUPS / NWAVE;        // 1 KiB load instructions per wave per stage
-  static_assert((NST - 2) * IPW <= 15, "vmcnt immediates below");
-  constexpr int BOFF = NL * ARR;             // offset of the Bh tile in a stage
+  constexpr int IPW = 2 * GROUPS / NWAVE;                // and per wave and stage
+  static_assert(2 * GROUPS % NWAVE == 0, "loads must divide evenly over the waves");
+  static_assert(NST >= 2 && NST <= 6 && (NST - 2) * IPW <= 15, "vmcnt immediates below");
+  constexpr int BOFF = NL * ARR;             // offset of the Bh tile in a slice
   __shared__ __attribute__((aligned(16))) char lds[NST * STAGE];
 
   int tm, tng;
@@ -243,45 +311,53 @@ __global__ __launch_bounds__(LpTile<NWC>::NTHR, 1) void contract_lp_kernel(const
   const int p = find_problem(tn_start, nprob, tng);
   const ContractLpProb a = probs[p];
   const int tn = tng - tn_start[p];
-  const int TC = a.CP / (Tile::BN / 2);     // column tiles per branch
+  const int TC = a.CP / Tile::BN;           // column tiles per branch
   const int branch = tn / TC;
   const int ct = tn - branch * TC;
   const int m0 = tm * BM;
-  const int c0 = ct * (Tile::BN / 2);                        // first complex column within the branch
-  const size_t prow = ((size_t)branch * a.CP + c0) * 2;      // first packed row of the tile
+  const int c0 = ct * Tile::BN;                              // first complex column within the branch
+  const size_t prow = (size_t)branch * a.CP + c0;            // first packed row of the tile
   const size_t cblk = prow >> 8;                             // its 256-row block
-  const int crow = (int)(prow & 255);                        // and row within the block (0 or 128)
+  const int crow = (int)(prow & 255);                        // and row within the block (a multiple of BN)
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wr = (wave / NWC) * 64;
-  const int wc = (wave % NWC) * 128;  // real columns
+  const int wc = (wave % NWC) * 64;  // complex columns
   const int half = lane >> 5;
   const int j = lane & 31;
 
-  // This wave's load instructions: tile q, row group rg (32 rows = 1 KiB).
-  const size_t kbs = (size_t)(a.Kp / BK) * 4096;  // elements per 256-row block
-  const T* src[IPW];
-  int ldst[IPW];
+  // This wave's load instructions: slice u, tile q, row group rg (32 rows =
+  // 1 KiB).  All are uniform over the wave, so each load goes through a buffer
+  // descriptor (scalar registers) based at the tile's 256-row block; the K
+  // position is a scalar offset and each lane keeps one 32-bit byte offset.
+  const size_t kbs = (size_t)(a.Kp / BK) * 8192;  // bytes per 256-row block
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
+  __amdgpu_buffer_rsrc_t rsrc[IPW];
+  int voff[IPW], ldst[IPW], ksl[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
     int q, rg, dst;
-    load_slot<NWC>(wave * IPW + i, NL, q, rg, dst);
+    const int slot = wv * IPW + i, u = slot / GROUPS;
+    load_slot<NWC>(slot - u * GROUPS, NL, q, rg, dst);
     const bool is_b = q >= NL;
     const int qq = is_b ? q - NL : q;  // 0 = hi, 1 = lo
-    const T* base = is_b ? (const T*)(qq ? a.Bl : a.Bh) + cblk * kbs : (const T*)(qq ? a.Ll : a.Lh) + (size_t)tm * kbs;
+    const char* base = is_b ? (const char*)(qq ? a.Bl : a.Bh) + cblk * kbs
+                            : (const char*)(qq ? a.Ll : a.Lh) + (size_t)tm * kbs;
+    rsrc[i] = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0xFFFFFFFF, 0x00020000);
     const int row = rg * 32 + (lane >> 1) + (is_b ? crow : 0);
     const int lc = (lane & 1) ^ swz(row);
-    src[i] = base + row * 16 + lc * 8;
-    ldst[i] = dst;
+    voff[i] = row * 32 + lc * 16;
+    ldst[i] = u * SLICE + dst;
+    ksl[i] = u * 8192;
   }
   auto issue = [&](int kt) {
     char* st = lds + (kt % NST) * STAGE;
 #pragma unroll
     for (int i = 0; i < IPW; ++i)
-      __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)kt * 4096),
-                                       (__attribute__((address_space(3))) void*)(st + ldst[i]), 16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc[i], (__attribute__((address_space(3))) void*)(st + ldst[i]), 16,
+                                               voff[i], kt * 16384 + ksl[i], 0, 0);
   };
 
   floatx16 acc[2][4];
@@ -291,15 +367,15 @@ __global__ __launch_bounds__(LpTile<NWC>::NTHR, 1) void contract_lp_kernel(const
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = zero;
 
-  // The operands of one stage, read from LDS into registers.  Two sets
-  // alternate: while the MFMAs of stage kt run on one set, the LDS reads of
-  // stage kt+1 fill the other, so LDS time hides behind MFMA time instead of
+  // The operands of one slice, read from LDS into registers.  Two sets
+  // alternate: while the MFMAs of one slice run on one set, the LDS reads of
+  // the next fill the other, so LDS time hides behind MFMA time instead of
   // adding to it.
   struct Ops {
-    V8 ah[2], al[2], bh[4], bl[4];
+    V8 ah[2], al[2], bh[2], bl[2];
   };
-  auto lds_read = [&](int kt, Ops& o) {
-    const char* st = lds + (kt % NST) * STAGE;
+  auto lds_read = [&](int kt, int u, Ops& o) {
+    const char* st = lds + (kt % NST) * STAGE + u * SLICE;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       const int row = wr + rb * 32 + j;
@@ -307,103 +383,111 @@ __global__ __launch_bounds__(LpTile<NWC>::NTHR, 1) void contract_lp_kernel(const
       if (NL == 2) o.al[rb] = *reinterpret_cast<const V8*>(st + 1 * ARR + lds_off(row, half));
     }
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int row = wc + cb * 32 + j;
-      o.bh[cb] = *reinterpret_cast<const V8*>(st + BOFF + lds_off(row, half));
-      if (NB == 2) o.bl[cb] = *reinterpret_cast<const V8*>(st + BOFF + Tile::BARR + lds_off(row, half));
+    for (int b = 0; b < 2; ++b) {
+      const int row = wc + wave_col(b, j);
+      o.bh[b] = *reinterpret_cast<const V8*>(st + BOFF + lds_off(row, half));
+      if (NB == 2) o.bl[b] = *reinterpret_cast<const V8*>(st + BOFF + Tile::BARR + lds_off(row, half));
     }
   };
   auto mma = [&](const Ops& o) {
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int b = 0; b < 2; ++b) {
+      V8 bh = o.bh[b], bl;
+      if (NB == 2) bl = o.bl[b];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        acc[rb][cb] = Vec8<T>::mfma(o.ah[rb], o.bh[cb], acc[rb][cb]);
-        if (NB == 2) acc[rb][cb] = Vec8<T>::mfma(o.ah[rb], o.bl[cb], acc[rb][cb]);
-        if (NL == 2) acc[rb][cb] = Vec8<T>::mfma(o.al[rb], o.bh[cb], acc[rb][cb]);
+      for (int p = 0; p < 2; ++p) {
+        if (p == 1) {
+          bh = turn(bh);
+          if (NB == 2) bl = turn(bl);
+        }
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          floatx16& c = acc[rb][2 * b + p];
+          c = Vec8<T>::mfma(o.ah[rb], bh, c);
+          if (NB == 2) c = Vec8<T>::mfma(o.ah[rb], bl, c);
+          if (NL == 2) c = Vec8<T>::mfma(o.al[rb], bh, c);
+        }
       }
+    }
   };
   // Make stage s readable by every wave: wait for this wave's own loads of
   // stage s (the `issued - 1 - s` stages issued after it may stay in flight)
-  // and for this wave's LDS reads, then one barrier.  In the steady state
-  // `issued` = s + NST - 1 on entry, so the load issued after the barrier
-  // (stage s + NST - 1) goes into buffer (s - 1) % NST, the buffer of stage
-  // s - 1, whose LDS reads every wave issued in the previous step: the
-  // LDS-read wait before the barrier is what makes that overwrite safe.  It
-  // costs nothing (those reads were issued a whole stage of MFMAs earlier).
-  const int nkt = a.Kp / BK;  // a multiple of 4: Kp is a multiple of 64
+  // and for this wave's LDS reads, then one barrier; then issue the next
+  // stage into the buffer of stage s - 1, whose LDS reads every wave has
+  // finished (the LDS-read wait before the barrier; those reads were issued a
+  // slice of MFMAs earlier).
+  const int nst = a.Kp / (2 * BK);  // stages: at least 2 (Kp is a multiple of 64)
   int issued = 0;
   auto open_stage = [&](int s) {
     const int later = issued - 1 - s;
-    if (later >= 3) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(3 * IPW));
-    else if (later == 2) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(2 * IPW));
-    else if (later == 1) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(IPW));
+    if (later >= 4 && NST > 5) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(4 * IPW));
+    else if (later == 3 && NST > 4) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(3 * IPW));
+    else if (later == 2 && NST > 3) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(2 * IPW));
+    else if (later == 1 && NST > 2) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(IPW));
     else __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
     asm volatile("s_barrier" ::: "memory");
-    if (issued < nkt) issue(issued++);
+    if (issued < nst) issue(issued++);
   };
 
 #pragma unroll
-  for (int i = 0; i < NST - 1; ++i) issue(issued++);
+  for (int i = 0; i < NST - 1; ++i)
+    if (i < nst) issue(issued++);
   Ops o0, o1;
   open_stage(0);
-  lds_read(0, o0);
-  // Steady state: `issued` = s + NST - 1 at every open, so the wait keeps
-  // NST - 2 stages in flight and one stage is issued; as straight-line code
-  // (no branch in the step) the compiler keeps the MFMAs ahead of the
-  // barrier.  The last stages take the general step below.
+  lds_read(0, 0, o0);
+  // Steady state: `issued` = kt + NST at every step, so the wait keeps NST - 2
+  // stages in flight and one stage is issued; as straight-line code (no
+  // branch in the step) the compiler keeps the MFMAs ahead of the barrier.
+  // The last stages take the general step below.
   int kt = 0;
-  for (; kt + NST + 1 < nkt; kt += 2) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm((NST - 2) * IPW));
-    asm volatile("s_barrier" ::: "memory");
-    issue(issued++);
-    lds_read(kt + 1, o1);
+  for (; kt + NST < nst; ++kt) {
+    lds_read(kt, 1, o1);
     mma(o0);
+    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm((NST - 2) * IPW));
     asm volatile("s_barrier" ::: "memory");
     issue(issued++);
-    lds_read(kt + 2, o0);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_read(kt + 1, 0, o0);
     mma(o1);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  for (; kt < nkt; kt += 2) {
-    open_stage(kt + 1);  // kt + 1 < nkt: nkt is even
-    lds_read(kt + 1, o1);
+  for (; kt < nst; ++kt) {
+    lds_read(kt, 1, o1);
     mma(o0);
-    if (kt + 2 < nkt) {
-      open_stage(kt + 2);
-      lds_read(kt + 2, o0);
+    if (kt + 1 < nst) {
+      open_stage(kt + 1);
+      lds_read(kt + 1, 0, o0);
     }
     mma(o1);
   }
   __syncthreads();  // the stage buffers are reused below
 
-  // Epilogue 1: W.  Output lane (j, half) of a 32x32 block holds real column j
-  // and rows 8*(v/4) + 4*half + v%4.
-  const int ncols = a.d * a.chi_r;
-  float* Wf = reinterpret_cast<float*>(a.W);
-  const size_t wpitch = 2 * (size_t)ncols;
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int rc = wc + cb * 32 + j;  // real column within the tile
-      const int colc = c0 + (rc >> 1);
-      const size_t fcol = 2 * ((size_t)branch * a.chi_r + c0) + rc;
-      if (colc < a.chi_r) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int gr = m0 + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-          if (gr < rows) store_w(Wf + (size_t)gr * wpitch + fcol, acc[rb][cb][v]);
-        }
-      }
-    }
-  }
+  // Epilogue 1: W.
+  store_w_block(acc, a.W, (size_t)a.d * a.chi_r, m0 + wr, rows, (size_t)branch * a.chi_r + c0 + wc, c0 + wc, a.chi_r,
+                half, j);
   // Epilogue 2: partial weights per 64 complex columns; padded columns are
   // exact zeros.
   const int TP = a.CP / kPartCols;  // partials per branch
   store_partials<NWC>(acc, reinterpret_cast<float*>(lds), wave, wr, half, j, tid, m0, rows, a.qpart,
                       (size_t)a.d * TP, branch * TP + c0 / kPartCols);
 }
+
+#define MPS_LP_KERNEL(NAME, T, NPROD, NWC)                                                                        \
+  __global__ __launch_bounds__(LpTile<NWC>::NTHR, 3 - NWC) void NAME(                                             \
+      const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total, int tiles_m, int per_xcd,        \
+      int group_m, const ChunkArgs* chp) {                                                                        \
+    contract_lp_kernel<T, NPROD, NWC>(probs, tn_start, nprob, tn_total, tiles_m, per_xcd, group_m, chp);            \
+  }
+MPS_LP_KERNEL(contract_bf16x3_wide, bf16_t, 3, 2)
+MPS_LP_KERNEL(contract_bf16x3_narrow, bf16_t, 3, 1)
+MPS_LP_KERNEL(contract_fp16x3_wide, f16_t, 3, 2)
+MPS_LP_KERNEL(contract_fp16x3_narrow, f16_t, 3, 1)
+MPS_LP_KERNEL(contract_fp16x2_wide, f16_t, 2, 2)
+MPS_LP_KERNEL(contract_fp16x2_narrow, f16_t, 2, 1)
+MPS_LP_KERNEL(contract_fp16_wide, f16_t, 1, 2)
+MPS_LP_KERNEL(contract_fp16_narrow, f16_t, 1, 1)
+#undef MPS_LP_KERNEL
 
 // ------------------------------------------------------------ fp16f8 ----
 
@@ -414,6 +498,22 @@ typedef int intx8 __attribute__((ext_vector_type(8)));
 // (the common factor of both corrections), 2^0 on the site tensor's.
 constexpr int kScale8L = 127 - 19;
 constexpr int kScale8B = 127;
+
+// turn (above) for a pair plane's E4M3 codes (groups of 8 bytes) and an E2M3
+// record's codes (dwords 0..2 real, 3..5 imaginary parts; dword 6, the scale,
+// is shared: the maximum is the same).
+__device__ inline intx8 turn_e4m3(intx8 w) {
+  intx8 o;
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    o[i] = w[i + 1] ^ (int)0x80808080u;
+    o[i + 1] = w[i];
+  }
+  return o;
+}
+__device__ inline intx8 turn_e2m3(intx8 w) {
+  return intx8{w[3] ^ 0x20820820, w[4] ^ 0x08208208, w[5] ^ (int)0x82082082u, w[0], w[1], w[2], w[6], 0};
+}
 
 // Smallest power of two s with amax / s <= 448 (the largest finite E4M3
 // value), exponent clamped to the normal FP32 range; 1 for zero or a
@@ -517,17 +617,16 @@ __global__ __launch_bounds__(256) void pack_f16f8_kernel(const PackProb* probs, 
   f16_t* Bh = (f16_t*)a.Bh;
   unsigned char* B8 = (unsigned char*)a.Bl;
 #pragma unroll
-  for (int it = 0; it < 2 * PK_C * 8 / 256; ++it) {
+  for (int it = 0; it < PK_C * 8 / 256; ++it) {
     const int idx = it * 256 + tid;
-    const int rowl = idx >> 3, ch = idx & 7;
-    const int c = rowl >> 1, p = rowl & 1;
+    const int c = idx >> 3, ch = idx & 7;
     const float inv = inv_sh[c];
     float v[8];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const float2 z = tile[ch * 4 + m][c];
-      v[2 * m] = (p ? z.y : z.x) * inv;
-      v[2 * m + 1] = (p ? z.x : -z.y) * inv;
+      v[m] = z.x * inv;
+      v[4 + m] = -z.y * inv;
     }
     f16x8 h;
     float hf[8], lo[8];
@@ -537,7 +636,7 @@ __global__ __launch_bounds__(256) void pack_f16f8_kernel(const PackProb* probs, 
       hf[e] = (float)h[e];
       lo[e] = (v[e] - hf[e]) * 2048.f;
     }
-    const size_t orow = ((size_t)br * a.CP + c0 + c) * 2 + p;
+    const size_t orow = (size_t)br * a.CP + c0 + c;
     const int k = 2 * l0 + ch * 8;
     *reinterpret_cast<f16x8*>(Bh + kblk_off(orow, k, a.Kp)) = h;
     if constexpr (!F6) {
@@ -556,41 +655,48 @@ __global__ __launch_bounds__(256) void pack_f16f8_kernel(const PackProb* probs, 
       // a record that small flushes to zero)
       const int ke = max(e2m3_scale_exp(m), -108);
       const float inv2 = ldexpf(1.f, -ke);
-      uint64_t l8 = 0, h8 = 0;  // this thread's 8 low-part and 8 high-part codes, 6 bits each
+      // this thread's codes, 4 of 6 bits each: low and high parts, re and im
+      uint32_t c[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        l8 |= (uint64_t)e2m3_code(lo[e] * inv2) << (6 * e);
-        h8 |= (uint64_t)e2m3_code(hf[e] * inv2) << (6 * e);
+        c[2 * (e >> 2)] |= e2m3_code(lo[e] * inv2) << (6 * (e & 3));
+        c[2 * (e >> 2) + 1] |= e2m3_code(hf[e] * inv2) << (6 * (e & 3));
       }
-      // Site record: codes 0..15 the low part, 16..31 the high part, K 0..7
-      // of the slice from the thread with (k & 8) == 0, K 8..15 from its
-      // neighbour.  Both threads assemble the 192 code bits and each stores
-      // one 16-byte half: [l0 | l1 | h0 | h1] (48 bits each), then byte 24
-      // the scale (the corrections' common 2^-19 rides on the site's scale)
-      // and zeros.
-      const uint64_t pl = __shfl_xor(l8, 1), ph = __shfl_xor(h8, 1);
+      // Site record: the 8 real parts' low codes, their high codes, then the
+      // same of the imaginary parts; complex 0..3 of the slice from the
+      // thread with (k & 8) == 0, 4..7 from its neighbour.  Both threads
+      // assemble the 192 code bits and each stores one 16-byte half; byte 24
+      // is the scale (the corrections' common 2^-19 rides on the site's
+      // scale), zeros after.
       const int q = (k & 8) ? 1 : 0;
-      const uint64_t l0 = q ? pl : l8, l1 = q ? l8 : pl, h0 = q ? ph : h8, h1 = q ? h8 : ph;
+      uint32_t w[6];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t lo_o = __shfl_xor(c[2 * i], 1), hi_o = __shfl_xor(c[2 * i + 1], 1);
+        const uint32_t l0 = q ? lo_o : c[2 * i], l1 = q ? c[2 * i] : lo_o;
+        const uint32_t h0 = q ? hi_o : c[2 * i + 1], h1 = q ? c[2 * i + 1] : hi_o;
+        w[3 * i] = l0 | (l1 << 24);
+        w[3 * i + 1] = (l1 >> 8) | (h0 << 16);
+        w[3 * i + 2] = (h0 >> 16) | (h1 << 8);
+      }
       unsigned char* rec = B8 + pair_off(orow, k & ~15, a.Kp);
       if (q == 0)
-        *reinterpret_cast<uint4*>(rec) = make_uint4((uint32_t)l0, (uint32_t)(l0 >> 32) | (uint32_t)(l1 << 16),
-                                                    (uint32_t)(l1 >> 16), (uint32_t)h0);
+        *reinterpret_cast<uint4*>(rec) = make_uint4(w[0], w[1], w[2], w[3]);
       else
-        *reinterpret_cast<uint4*>(rec + 16) = make_uint4((uint32_t)(h0 >> 32) | (uint32_t)(h1 << 16),
-                                                         (uint32_t)(h1 >> 16), (uint32_t)(127 + ke - 19), 0u);
+        *reinterpret_cast<uint4*>(rec + 16) = make_uint4(w[4], w[5], (uint32_t)(127 + ke - 19), 0u);
     }
   }
 }
 
-// The fp16f8 contraction.  Same tile (256 x 256 real), waves, operand
-// loading (global_load_lds into a 5-slice LDS ring) and epilogue as
+// The fp16f8 contraction.  Same tile (256 x 128 complex), waves, operand
+// loading (global_load_lds into a 6-slice LDS ring) and epilogue as
 // contract_lp_kernel; a slice holds 16 real K of [Lh | L8 | Bh | B8].  The FP8
 // instruction takes 32 bytes per lane: lane half h of a row (column) reads
 // its 32-byte row of the pair plane from slice 2m + h, so one instruction
 // covers the slice pair (2m, 2m+1) and both correction products on it.  The
 // slices are made readable a pair at a time (one barrier per 32 real K):
-// while pair m is read and multiplied, slices 2m+2 .. 2m+4 are in flight,
-// and the loads issued after the barrier of pair m+1 (slices 2m+5, 2m+6)
+// while pair m is read and multiplied, slices 2m+2 .. 2m+5 are in flight,
+// and the loads issued after the barrier of pair m+1 (slices 2m+6, 2m+7)
 // refill the two buffers of pair m, whose LDS reads every wave has finished
 // (LDS-read wait before the barrier).
 // (The body is a device function template with one plain kernel per
@@ -599,12 +705,12 @@ template <int NWC, bool F6>
 __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total,
                                            int tiles_m, int per_xcd, int group_m, const ChunkArgs* chp) {
   typedef LpTile<NWC> Tile;
-  constexpr int NST = 5;  // the pair scheme below needs five slices
+  constexpr int NST = 6;  // three slice pairs: one in use, two in flight
   constexpr int BOFF = 2 * ARR;  // stage: Lh, L8 (pair plane), Bh, B8 (pair plane)
   constexpr int STAGE = 2 * ARR + 2 * Tile::BARR;
   constexpr int GROUPS = 2 * 8 + 2 * (Tile::BN / 32);
   constexpr int IPW = GROUPS / (4 * NWC);
-  static_assert(GROUPS % (4 * NWC) == 0 && IPW <= 15, "loads must divide evenly; vmcnt immediates");
+  static_assert(GROUPS % (4 * NWC) == 0 && 2 * IPW <= 15, "loads must divide evenly; vmcnt immediates");
   __shared__ __attribute__((aligned(16))) char lds[NST * STAGE];
 
   int tm, tng;
@@ -613,12 +719,12 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
   const int p = find_problem(tn_start, nprob, tng);
   const ContractLpProb a = probs[p];
   const int tn = tng - tn_start[p];
-  const int TC = a.CP / (Tile::BN / 2);  // column tiles per branch
+  const int TC = a.CP / Tile::BN;  // column tiles per branch
   const int branch = tn / TC;
   const int ct = tn - branch * TC;
   const int m0 = tm * BM;
-  const int c0 = ct * (Tile::BN / 2);
-  const size_t prow = ((size_t)branch * a.CP + c0) * 2;  // first packed row of the tile
+  const int c0 = ct * Tile::BN;
+  const size_t prow = (size_t)branch * a.CP + c0;  // first packed row of the tile
   const size_t cblk = prow >> 8;
   const int crow = (int)(prow & 255);
 
@@ -626,7 +732,7 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wr = (wave / NWC) * 64;
-  const int wc = (wave % NWC) * 128;
+  const int wc = (wave % NWC) * 64;
   const int half = lane >> 5;
   const int j = lane & 31;
 
@@ -669,27 +775,29 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
     for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = zero;
 
   struct Ops16 {
-    f16x8 a[2], b[4];
+    f16x8 a[2], b[2];
   };
   struct Ops8 {
-    intx8 a[2], b[4];
+    intx8 a[2], b[2];
   };
-  // LDS read offsets.  Rows r and r + 32 have the same swizzle (it depends
-  // on row bits 2 and 3 only), so one offset per operand and chunk serves
-  // every row block, the blocks being 1 KiB apart (immediate offsets).
+  // LDS read offsets.  Rows r, r + 16 and r + 32 have the same swizzle (it
+  // depends on row bits 2 and 3 only), so one offset per operand and chunk
+  // serves every block: row blocks 1 KiB apart, column blocks 16 rows (512
+  // bytes) apart (immediate offsets).
   const int sj = swz(j);
+  const int jc = wc + wave_col(0, j);
   const unsigned a_h = (unsigned)((wr + j) * 32 + ((half ^ sj) << 4));           // Lh, chunk `half`
-  const unsigned b_h = (unsigned)(BOFF + (wc + j) * 32 + ((half ^ sj) << 4));     // Bh, chunk `half`
+  const unsigned b_h = (unsigned)(BOFF + jc * 32 + ((half ^ sj) << 4));           // Bh, chunk `half`
   const unsigned a8_0 = (unsigned)(ARR + (wr + j) * 32 + (sj << 4));              // L8, chunk 0
   const unsigned a8_1 = (unsigned)(ARR + (wr + j) * 32 + ((1 ^ sj) << 4));        // L8, chunk 1
-  const unsigned b8_0 = (unsigned)(BOFF + Tile::BARR + (wc + j) * 32 + (sj << 4));        // B8, chunk 0
-  const unsigned b8_1 = (unsigned)(BOFF + Tile::BARR + (wc + j) * 32 + ((1 ^ sj) << 4));  // B8, chunk 1
+  const unsigned b8_0 = (unsigned)(BOFF + Tile::BARR + jc * 32 + (sj << 4));        // B8, chunk 0
+  const unsigned b8_1 = (unsigned)(BOFF + Tile::BARR + jc * 32 + ((1 ^ sj) << 4));  // B8, chunk 1
   auto read16 = [&](int kt, Ops16& o) {
     const char* st = lds + (kt % NST) * STAGE;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) o.a[rb] = *reinterpret_cast<const f16x8*>(st + a_h + rb * 1024);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) o.b[cb] = *reinterpret_cast<const f16x8*>(st + b_h + cb * 1024);
+    for (int b = 0; b < 2; ++b) o.b[b] = *reinterpret_cast<const f16x8*>(st + b_h + b * 512);
   };
   auto cat = [](intx4 x, intx4 y) -> intx8 { return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7); };
   // FP6 records: dwords 0..5 codes, dword 6 scale, dword 7 zero (read as
@@ -711,51 +819,58 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
                       *reinterpret_cast<const intx4*>(st + a8_1 + rb * 1024));
     }
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
+    for (int b = 0; b < 2; ++b) {
       if constexpr (F6)
-        o.b[cb] = rec6(st + b8_0 + cb * 1024, st + b8_1 + cb * 1024);
+        o.b[b] = rec6(st + b8_0 + b * 512, st + b8_1 + b * 512);
       else
-        o.b[cb] = cat(*reinterpret_cast<const intx4*>(st + b8_0 + cb * 1024),
-                      *reinterpret_cast<const intx4*>(st + b8_1 + cb * 1024));
+        o.b[b] = cat(*reinterpret_cast<const intx4*>(st + b8_0 + b * 512),
+                     *reinterpret_cast<const intx4*>(st + b8_1 + b * 512));
     }
   };
+  // Per block of 32 columns: the real parts with the operand as read, then
+  // the imaginary parts with it turned.
   auto mma16 = [&](const Ops16& o) {
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int cb = 0; cb < 4; ++cb) {
+      const f16x8 b = cb & 1 ? turn(o.b[cb >> 1]) : o.b[cb >> 1];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o.a[rb], o.b[cb], acc[rb][cb], 0, 0, 0);
+      for (int rb = 0; rb < 2; ++rb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o.a[rb], b, acc[rb][cb], 0, 0, 0);
+    }
   };
   // FP6: formats 2 (E2M3) on both sides; the first six dwords of a lane's
   // record are its 32 codes, the low byte of the seventh its scale.
   auto mma8 = [&](const Ops8& o) {
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int cb = 0; cb < 4; ++cb) {
+      const intx8 b = cb & 1 ? (F6 ? turn_e2m3(o.b[cb >> 1]) : turn_e4m3(o.b[cb >> 1])) : o.b[cb >> 1];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
+      for (int rb = 0; rb < 2; ++rb) {
         if constexpr (F6)
-          acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o.a[rb], o.b[cb], acc[rb][cb], 2, 2, 0,
-                                                                        o.a[rb][6], 0, o.b[cb][6]);
+          acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o.a[rb], b, acc[rb][cb], 2, 2, 0, o.a[rb][6],
+                                                                        0, b[6]);
         else
-          acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o.a[rb], o.b[cb], acc[rb][cb], 0, 0, 0,
-                                                                        kScale8L, 0, kScale8B);
+          acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o.a[rb], b, acc[rb][cb], 0, 0, 0, kScale8L, 0,
+                                                                        kScale8B);
       }
+    }
   };
 
   const int nkt = a.Kp / BK;  // a multiple of 4
   const int npair = nkt >> 1;
   int issued = 0;
-  // Pair m readable: slices 2m and 2m+1 landed (slice 2m+2, issued after
+  // Pair m readable: slices 2m and 2m+1 landed (pair m+1, issued after
   // them, may stay in flight), this wave's LDS reads done, one barrier; then
   // the next two slices are issued into the buffers of pair m-1.
   auto open_pair = [&](int m) {
-    if (issued > 2 * m + 2) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(IPW));
+    if (issued > 2 * m + 2) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(2 * IPW));
     else __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
     asm volatile("s_barrier" ::: "memory");
     if (issued < nkt) issue(issued++);
     if (issued < nkt) issue(issued++);
   };
 #pragma unroll
-  for (int i = 0; i < 3; ++i) issue(issued++);
+  for (int i = 0; i < 4; ++i) issue(issued++);  // nkt >= 4
   // Operand registers: e (even slice, fp16), h (odd slice, fp16), f (FP8
   // operands of the pair); at most two of them are live at a time, each
   // read while the MFMAs of another run.
@@ -776,12 +891,12 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
   // before mma16(h) (their registers are free once mma8(f) has issued), so
   // that they have the whole of mma16(h) and mma16(e') to arrive; the
   // reads of h may mix with the MFMAs of e.
-  for (; m + 3 < npair; ++m) {
+  auto step = [&](int m) {
     mma16(e);
     read16(2 * m + 1, h);
     mma8(f);
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(IPW));
+    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(2 * IPW));
     asm volatile("s_barrier" ::: "memory");
     issue(issued++);
     issue(issued++);
@@ -790,6 +905,10 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
     read8(m + 1, f);
     mma16(h);
     __builtin_amdgcn_sched_barrier(0);
+  };
+  for (; m + 4 < npair; m += 2) {
+    step(m);
+    step(m + 1);
   }
   for (; m < npair; ++m) {
     mma16(e);
@@ -810,32 +929,15 @@ __device__ inline void contract_f16f8_body(const ContractLpProb* probs, const in
   // Column scales: W[:, c] = s_c * acc (exact, a power of two).
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb) {
-    const float sc = a.colscale[(size_t)branch * a.CP + c0 + ((wc + cb * 32 + j) >> 1)];
+    const float sc = a.colscale[(size_t)branch * a.CP + c0 + wc + wave_col(cb >> 1, j)];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[rb][cb][v] *= sc;
   }
 
-  const int ncols = a.d * a.chi_r;
-  float* Wf = reinterpret_cast<float*>(a.W);
-  const size_t wpitch = 2 * (size_t)ncols;
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int rc = wc + cb * 32 + j;
-      const int colc = c0 + (rc >> 1);
-      const size_t fcol = 2 * ((size_t)branch * a.chi_r + c0) + rc;
-      if (colc < a.chi_r) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int gr = m0 + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-          if (gr < rows) store_w(Wf + (size_t)gr * wpitch + fcol, acc[rb][cb][v]);
-        }
-      }
-    }
-  }
+  store_w_block(acc, a.W, (size_t)a.d * a.chi_r, m0 + wr, rows, (size_t)branch * a.chi_r + c0 + wc, c0 + wc, a.chi_r,
+                half, j);
   const int TP = a.CP / kPartCols;  // partials per branch
   store_partials<NWC>(acc, reinterpret_cast<float*>(lds), wave, wr, half, j, tid, m0, rows, a.qpart,
                       (size_t)a.d * TP, branch * TP + c0 / kPartCols);
@@ -887,25 +989,6 @@ hipError_t launch_pack_t(const PackProb* probs, const int* blk_start, int nprob,
     return hipGetLastError();                                                                                 \
   } while (0)
 
-template <typename T, int NPROD>
-hipError_t launch_contract_t(int tile, const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total,
-                             const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
-  if (tile == kTileNarrow) MPS_CONTRACT_LAUNCH((contract_lp_kernel<T, NPROD, 1>), LpTile<1>::NTHR);
-  MPS_CONTRACT_LAUNCH((contract_lp_kernel<T, NPROD, 2>), LpTile<2>::NTHR);
-}
-
-hipError_t launch_f16f8(int tile, const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total,
-                        const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
-  if (tile == kTileNarrow) MPS_CONTRACT_LAUNCH(contract_f16f8_narrow, LpTile<1>::NTHR);
-  MPS_CONTRACT_LAUNCH(contract_f16f8_wide, LpTile<2>::NTHR);
-}
-
-hipError_t launch_f16f6(int tile, const ContractLpProb* probs, const int* tn_start, int nprob, int tn_total,
-                        const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
-  if (tile == kTileNarrow) MPS_CONTRACT_LAUNCH(contract_f16f6_narrow, LpTile<1>::NTHR);
-  MPS_CONTRACT_LAUNCH(contract_f16f6_wide, LpTile<2>::NTHR);
-}
-
 }  // namespace
 
 hipError_t launch_colscale(const PackProb* probs, const int* cm_start, int nprob, int cm_total, hipStream_t s) {
@@ -933,15 +1016,18 @@ hipError_t launch_pack_lp(int form, const PackProb* probs, const int* blk_start,
 
 hipError_t launch_contract_lp(int form, int tile, const ContractLpProb* probs, const int* tn_start, int nprob,
                               int tn_total, const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
-  if (form == kFp16F8) return launch_f16f8(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
-  if (form == kFp16F6) return launch_f16f6(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
-  if (form == kBf16x3)
-    return launch_contract_t<bf16_t, 3>(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
-  if (form == kFp16x3)
-    return launch_contract_t<f16_t, 3>(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
-  if (form == kFp16x2)
-    return launch_contract_t<f16_t, 2>(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
-  return launch_contract_t<f16_t, 1>(tile, probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
+#define MPS_CONTRACT_FORM(NAME)                                                      \
+  do {                                                                               \
+    if (tile == kTileNarrow) MPS_CONTRACT_LAUNCH(NAME##_narrow, LpTile<1>::NTHR);    \
+    MPS_CONTRACT_LAUNCH(NAME##_wide, LpTile<2>::NTHR);                               \
+  } while (0)
+  if (form == kFp16F8) MPS_CONTRACT_FORM(contract_f16f8);
+  if (form == kFp16F6) MPS_CONTRACT_FORM(contract_f16f6);
+  if (form == kBf16x3) MPS_CONTRACT_FORM(contract_bf16x3);
+  if (form == kFp16x3) MPS_CONTRACT_FORM(contract_fp16x3);
+  if (form == kFp16x2) MPS_CONTRACT_FORM(contract_fp16x2);
+  MPS_CONTRACT_FORM(contract_fp16);
+#undef MPS_CONTRACT_FORM
 }
 
 }  // namespace mps

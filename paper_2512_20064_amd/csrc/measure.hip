@@ -58,7 +58,6 @@ struct LWriter<kOutF32> {
   float2* dst;
   int n;
   __device__ LWriter(const MeasureProb& a, int row) : dst(a.Lout + (size_t)row * a.chi_r), n(a.chi_r) {}
-  __device__ void put(int r, float x, float y) { dst[r] = make_float2(x, y); }
   // complex r4 .. r4+3 (r4 a multiple of 4; entries at or past chi_r are dropped)
   __device__ void put4(int r4, const float2 (&v)[4]) {
     if (r4 + 4 <= n && (n & 1) == 0) {
@@ -71,7 +70,6 @@ struct LWriter<kOutF32> {
         if (r4 + j < n) dst[r4 + j] = v[j];
     }
   }
-  __device__ void pad(const MeasureProb&, int, int) {}
   __device__ void pad_from(int, int, int) {}
 };
 
@@ -84,36 +82,22 @@ struct SplitWriter {
   int ld;
   __device__ SplitWriter(const MeasureProb& a, int r)
       : hi((uint32_t*)a.Lh), lo((uint32_t*)a.Ll), row((size_t)r), ld(a.ld_out) {}
-  // x = hi + lo with hi = T(x) (round to nearest even), lo = T(x - hi);
-  // (re, im) of complex r are K elements 2r, 2r+1: one 32-bit word.
-  __device__ void put(int r, float x, float y) {
-    const T xh = (T)x, yh = (T)y;
-    const T xl = (T)(x - (float)xh), yl = (T)(y - (float)yh);
-    const size_t w = kblk_off(row, 2 * r, ld) >> 1;
-    hi[w] = pack2(xh, yh);
-    lo[w] = pack2(xl, yl);
-  }
+  // x = hi + lo with hi = T(x) (round to nearest even), lo = T(x - hi).
   // complex r4 .. r4+3 (r4 a multiple of 4, zeros past chi_r): K values
-  // 2*r4 .. 2*r4+7, half of one 16-K block, one 16-byte store per plane.
+  // 2*r4 .. 2*r4+7 (real parts, then imaginary), half of one 16-K block, one
+  // 16-byte store per plane.
   __device__ void put4(int r4, const float2 (&v)[4]) {
     uint32_t h[4], l[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const T xh = (T)v[j].x, yh = (T)v[j].y;
+      const float x = j < 2 ? v[2 * j].x : v[2 * j - 4].y, y = j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y;
+      const T xh = (T)x, yh = (T)y;
       h[j] = pack2(xh, yh);
-      l[j] = pack2((T)(v[j].x - (float)xh), (T)(v[j].y - (float)yh));
+      l[j] = pack2((T)(x - (float)xh), (T)(y - (float)yh));
     }
     const size_t w = kblk_off(row, 2 * r4, ld) >> 1;
     *reinterpret_cast<uint4*>(hi + w) = make_uint4(h[0], h[1], h[2], h[3]);
     *reinterpret_cast<uint4*>(lo + w) = make_uint4(l[0], l[1], l[2], l[3]);
-  }
-  // zeros for K in [2 chi_r, ld); lane sl of a group of W lanes
-  __device__ void pad(const MeasureProb& a, int sl, int W) {
-    for (int k = 2 * a.chi_r + 2 * sl; k < ld; k += 2 * W) {
-      const size_t w = kblk_off(row, k, ld) >> 1;
-      hi[w] = 0u;
-      lo[w] = 0u;
-    }
   }
   // zeros for K in [k0, ld), k0 a multiple of 8
   __device__ void pad_from(int k0, int sl, int W) {
@@ -143,22 +127,15 @@ struct LWriter<kOutF16> {
   size_t row;
   int ld;
   __device__ LWriter(const MeasureProb& a, int r) : hi((uint32_t*)a.Lh), row((size_t)r), ld(a.ld_out) {}
-  __device__ void put(int r, float x, float y) {
-    const f16_t xh = (f16_t)x, yh = (f16_t)y;
-    hi[kblk_off(row, 2 * r, ld) >> 1] =
-        (uint32_t)__builtin_bit_cast(uint16_t, xh) | ((uint32_t)__builtin_bit_cast(uint16_t, yh) << 16);
-  }
   __device__ void put4(int r4, const float2 (&v)[4]) {
     uint32_t h[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const f16_t xh = (f16_t)v[j].x, yh = (f16_t)v[j].y;
+      const f16_t xh = (f16_t)(j < 2 ? v[2 * j].x : v[2 * j - 4].y);
+      const f16_t yh = (f16_t)(j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y);
       h[j] = (uint32_t)__builtin_bit_cast(uint16_t, xh) | ((uint32_t)__builtin_bit_cast(uint16_t, yh) << 16);
     }
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r4, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
-  }
-  __device__ void pad(const MeasureProb& a, int sl, int W) {
-    for (int k = 2 * a.chi_r + 2 * sl; k < ld; k += 2 * W) hi[kblk_off(row, k, ld) >> 1] = 0u;
   }
   __device__ void pad_from(int k0, int sl, int W) {
     for (int k = k0 + 8 * sl; k < ld; k += 8 * W)
@@ -189,15 +166,6 @@ struct LWriter<kOutF16F8> {
     c_hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(xf * 256.f, yf * 256.f, 0, false) & 0xFFFFu;
     c_lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32((x - xf) * 524288.f, (y - yf) * 524288.f, 0, false) & 0xFFFFu;
   }
-  __device__ void put(int r, float x, float y) {
-    f16_t xh, yh;
-    unsigned ch, cl;
-    codes2(x, y, xh, yh, ch, cl);
-    hi[kblk_off(row, 2 * r, ld) >> 1] = pack2(xh, yh);
-    const size_t o = pair_off(row, 2 * r, ld);
-    *reinterpret_cast<uint16_t*>(p8 + o) = (uint16_t)ch;
-    *reinterpret_cast<uint16_t*>(p8 + o + 16) = (uint16_t)cl;
-  }
   // complex r4 .. r4+3: K values 2*r4 .. 2*r4+7, half of a 16-K slice
   __device__ void put4(int r4, const float2 (&v)[4]) {
     uint32_t h[4];
@@ -205,21 +173,13 @@ struct LWriter<kOutF16F8> {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       f16_t xh, yh;
-      codes2(v[j].x, v[j].y, xh, yh, ch[j], cl[j]);
+      codes2(j < 2 ? v[2 * j].x : v[2 * j - 4].y, j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y, xh, yh, ch[j], cl[j]);
       h[j] = pack2(xh, yh);
     }
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r4, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
     const size_t o = pair_off(row, 2 * r4, ld);
     *reinterpret_cast<uint2*>(p8 + o) = make_uint2(ch[0] | (ch[1] << 16), ch[2] | (ch[3] << 16));
     *reinterpret_cast<uint2*>(p8 + o + 16) = make_uint2(cl[0] | (cl[1] << 16), cl[2] | (cl[3] << 16));
-  }
-  __device__ void pad(const MeasureProb& a, int sl, int W) {
-    for (int k = 2 * a.chi_r + 2 * sl; k < ld; k += 2 * W) {
-      hi[kblk_off(row, k, ld) >> 1] = 0u;
-      const size_t o = pair_off(row, k, ld);
-      *reinterpret_cast<uint16_t*>(p8 + o) = 0;
-      *reinterpret_cast<uint16_t*>(p8 + o + 16) = 0;
-    }
   }
   __device__ void pad_from(int k0, int sl, int W) {
     for (int k = k0 + 8 * sl; k < ld; k += 8 * W) {
@@ -232,9 +192,9 @@ struct LWriter<kOutF16F8> {
 };
 
 // fp16f6 writer: the fp16 plane as fp16f8, and per 16-K slice one E2M3
-// record of the 32 values Lh * 2^8 (codes 0..15) and (x - Lh) * 2^19 (codes
-// 16..31) divided by the record's power of two 2^k (E8M0 code 127 + k in
-// byte 24).  A record needs the whole slice, so this writer takes pieces of
+// record of the 32 values Lh * 2^8 and (x - Lh) * 2^19 (codes 0..7 and 8..15
+// the real parts', 16..23 and 24..31 the imaginary parts') divided by the
+// record's power of two 2^k (E8M0 code 127 + k in byte 24).  A record needs the whole slice, so this writer takes pieces of
 // 8 complex (put8) and the measurement never hands it single values (the
 // displaced measurement forms whole slices for it too).
 template <>
@@ -252,14 +212,18 @@ struct LWriter<kOutF16F6> {
     float m = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const f16_t xh = (f16_t)v[j].x, yh = (f16_t)v[j].y;
+      // word j of the plane: re 0 1, re 2 3, im 0 1, im 2 3, then the same of complex 4 .. 7
+      const int e = 4 * (j >> 2) + 2 * (j & 1);
+      const float x = j & 2 ? v[e].y : v[e].x, y = j & 2 ? v[e + 1].y : v[e + 1].x;
+      const f16_t xh = (f16_t)x, yh = (f16_t)y;
       h[j] = (uint32_t)__builtin_bit_cast(uint16_t, xh) | ((uint32_t)__builtin_bit_cast(uint16_t, yh) << 16);
       const float xf = (float)xh, yf = (float)yh;
-      hv[2 * j] = xf * 256.f;
-      hv[2 * j + 1] = yf * 256.f;
-      lv[2 * j] = (v[j].x - xf) * 524288.f;
-      lv[2 * j + 1] = (v[j].y - yf) * 524288.f;
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(hv[2 * j]), fabsf(hv[2 * j + 1])), fmaxf(fabsf(lv[2 * j]), fabsf(lv[2 * j + 1]))));
+      const int t = (j & 2 ? 8 : 0) + e;  // 0..7 the real parts, 8..15 the imaginary ones
+      hv[t] = xf * 256.f;
+      hv[t + 1] = yf * 256.f;
+      lv[t] = (x - xf) * 524288.f;
+      lv[t + 1] = (y - yf) * 524288.f;
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(hv[t]), fabsf(hv[t + 1])), fmaxf(fabsf(lv[t]), fabsf(lv[t + 1]))));
     }
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r8, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r8 + 8, ld) >> 1)) = make_uint4(h[4], h[5], h[6], h[7]);
@@ -268,8 +232,8 @@ struct LWriter<kOutF16F6> {
     unsigned c[32];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      c[e] = e2m3_code(hv[e] * inv);
-      c[16 + e] = e2m3_code(lv[e] * inv);
+      c[(e & 7) + 2 * (e & 8)] = e2m3_code(hv[e] * inv);
+      c[(e & 7) + 2 * (e & 8) + 8] = e2m3_code(lv[e] * inv);
     }
     e2m3_store_record(p6 + pair_off(row, 2 * r8, ld), c, (unsigned)(127 + k));
   }

@@ -53,8 +53,15 @@ __host__ __device__ inline int lp_col_tiles(int CP, int tile) { return CP / (til
 // a matrix of R rows (a multiple of 256) and Kp columns (a multiple of 16) is
 // a grid of 256 x 16 tiles, each tile 8 KiB contiguous with its rows 32 bytes
 // apart, tiles of one row block consecutive in K.  One pipeline stage of the
-// contraction is then one contiguous 8 KiB block per operand, which the
-// loads stream as whole cache lines.
+// contraction is then one contiguous block per operand, which the loads
+// stream as whole cache lines.  Each run of 8 K values belongs to 4
+// consecutive complex numbers: their real parts, then their imaginary parts
+// (the MFMA's sum over a lane's 8 values does not depend on their order).
+//
+// A row of the packed site tensor is one complex column of a branch, its K
+// values the embedding's (Re a, -Im a); the column's other row, (Im a, Re a),
+// is formed in registers (contract_lp.hip, turn).  That halves the site
+// tensor's packing, memory, L2 and LDS traffic against storing both.
 __host__ __device__ inline size_t kblk_off(size_t r, int k, int Kp) {
   return ((r >> 8) * (size_t)(Kp >> 4) + (size_t)(k >> 4)) * 4096 + (r & 255) * 16 + (k & 15);
 }
@@ -85,7 +92,9 @@ __host__ __device__ inline size_t kblk_off(size_t r, int k, int Kp) {
 // rate.  E2M3 spans only 2^-3 .. 7.5, so each 32-value lane record gets its
 // own power-of-two scale s: the record of (row or column, 16-K slice) holds
 // the 32 six-bit codes of the FP8 pair-plane values divided by s (code p at
-// bits 6p .. 6p+5, little-endian over bytes 0 .. 23), then the E8M0 code of
+// bits 6p .. 6p+5, little-endian over bytes 0 .. 23; codes 0..15 the real
+// parts of the slice's 8 complex, 16..31 the imaginary ones, each 8 codes of
+// one part and 8 of the other in the pair planes' order), then the E8M0 code of
 // s in byte 24 (the site tensor's carries the common 2^-19 as well: code
 // 127 + log2(s) - 19), bytes 25 .. 31 zero.  The MFMA applies a lane's scale
 // to the 32 values that lane holds.
@@ -130,7 +139,7 @@ struct ContractProb {
 
 struct PackProb {
   const float2* A;   // [K][d][chi_r] complex site tensor
-  void* Bh;          // [d*CP*2][Kp] 16-bit real embedding, K contiguous
+  void* Bh;          // [d*CP][Kp] 16-bit rows (Re a, -Im a), K contiguous
   void* Bl;          // low parts (split forms; kFp16F8: the FP8 pair plane; kFp16F6: the FP6 records)
   int K, d, chi_r, CP, Kp;
   float* colscale;   // kFp16F8, kFp16F6: [d*CP] power-of-two scale s_c per complex column
@@ -140,7 +149,7 @@ struct PackProb {
 __host__ __device__ inline int colmax_blocks(int K) { return K < 64 * 16 ? (K + 63) / 64 : 16; }
 
 struct ContractLpProb {
-  const void* Lh;    // [rows_alloc][Kp] 16-bit left vectors (interleaved re, im), K padded with 0
+  const void* Lh;    // [rows_alloc][Kp] 16-bit left vectors, K padded with 0
   const void* Ll;    // low parts (bf16x3 only)
   const void* Bh;    // packed site tensor
   const void* Bl;
