@@ -189,9 +189,9 @@ struct InitProb {
 };
 
 // Persistent small-bond sweep (FP32): chains with chi_k <= kSmallChi and
-// d_k <= kSmallD at every site go through all their sites in one launch, 32
+// d_k <= kSmallD at every site go through all their sites in one launch, 16
 // samples per workgroup (an "item"), left vectors and W kept in LDS.
-constexpr int kSmallRows = 32;
+constexpr int kSmallRows = 16;
 constexpr int kSmallChi = 32;
 constexpr int kSmallD = 4;
 
