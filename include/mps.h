@@ -154,11 +154,15 @@ typedef struct {
   int32_t graph;
   /* 0: chains whose bonds stay <= 32 and physical dimensions <= 4 (sites
    * device-resident complex64, no displacement) go through all their sites in
-   * one persistent launch per chunk, 32 samples per workgroup, left vectors
+   * one persistent launch per chunk, 16 samples per workgroup, left vectors
    * and W kept in LDS, with the FP32 contraction whatever the precision form
    * (at these bonds it is faster than the 16-bit forms and at least as
-   * accurate); 1: every chain takes the per-site launches of the handle's
-   * precision form.                                                        */
+   * accurate); and, in the split forms, chains whose bonds stay <= 256 and
+   * whose sites all have d * ceil(chi_r / 64) <= 16 go through all their
+   * sites in one persistent launch with the arithmetic and the bits of the
+   * per-site launches (their sites are packed once per call, up to 1 GiB);
+   * 1: every chain takes the per-site launches of the handle's precision
+   * form.                                                                   */
   int32_t fused_small;
   /* Optional per-sample displacement of the physical index (MPS-based GBS
    * simulation, Section 3.4.1): DEVICE complex64 mu[N][M] (row of the call,
@@ -184,9 +188,13 @@ typedef struct {
 } mps_chain;
 
 typedef struct {
-  int64_t contract_launches;  /* contraction kernels launched by the last call     */
+  int64_t contract_launches;  /* contraction kernels launched by the last call      */
+                              /* (the persistent medium-bond kernel counts one      */
+                              /* contraction and one measurement per site and       */
+                              /* chunk, and its time as contraction)                */
   int64_t measure_launches;   /* measurement kernels launched by the last call     */
-  int64_t pack_launches;      /* site-tensor packing kernels (16-bit forms)         */
+  int64_t pack_launches;      /* site-tensor packing kernels (16-bit forms; one for */
+                              /* all sites of the medium-bond kernel's chains)      */
   double contract_ms;         /* summed event time of those launches (profile=1)    */
   double measure_ms;
   double pack_ms;

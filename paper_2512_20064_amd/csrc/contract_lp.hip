@@ -43,34 +43,12 @@
 // whole sweep: 48.5 -> 42.7 ms and 14.9 -> 13.9 ms).
 
 #include "e2m3.h"
+#include "lp_ops.h"
 #include "sweep.h"
 #include "tiling.h"
 
 namespace mps {
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16_t;
-typedef _Float16 f16_t;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-template <typename T>
-struct Vec8;
-template <>
-struct Vec8<bf16_t> {
-  typedef bf16x8 type;
-  static __device__ floatx16 mfma(type a, type b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Vec8<f16_t> {
-  typedef f16x8 type;
-  static __device__ floatx16 mfma(type a, type b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-};
 
 // ---------------------------------------------------------------- pack ----
 
@@ -145,29 +123,6 @@ struct LpTile {
   static constexpr int BARR = BN * BK * 2;        // bytes of one site-tensor tile in a stage
 };
 
-// A wave's 64 complex columns as MFMA blocks: acc[rb][2 b] and acc[rb][2 b + 1]
-// hold the real and imaginary parts of the 32 columns of block b, lane j the
-// column wave_col(b, j).  This order keeps the partial weights' additions
-// those of 16-column blocks taken in order (store_partials).
-__device__ inline int wave_col(int b, int j) { return (j >> 4) * 32 + b * 16 + (j & 15); }
-
-// The p = 1 row of the embedding from the p = 0 row, per lane: (x, y) ->
-// (-y, x).  With the real parts of 4 complex in one half of a lane's 8 K
-// values and the imaginary ones in the other (kblk_off) that is an exchange
-// of the halves and two sign flips.
-template <typename V8>
-__device__ inline V8 turn(V8 v) {
-  typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-  const uintx4 w = __builtin_bit_cast(uintx4, v);
-  return __builtin_bit_cast(V8, uintx4{w[2] ^ 0x80008000u, w[3] ^ 0x80008000u, w[0], w[1]});
-}
-
-// LDS rows are 32 bytes (16 K values = 2 chunks of 16 bytes).  The chunk is
-// XOR-swizzled by row bits 2 and 3 so that the 16-byte reads of 8 or 16
-// consecutive lanes (consecutive rows, same chunk) land in distinct banks.
-__device__ inline int swz(int row) { return ((row >> 2) ^ (row >> 3)) & 1; }
-__device__ inline int lds_off(int row, int chunk) { return row * 32 + ((chunk ^ swz(row)) << 4); }
-
 // s_waitcnt immediate: at most n vector-memory operations of this wave still
 // outstanding, and every LDS read of this wave returned (lgkmcnt 0); expcnt
 // is not waited on.
@@ -191,37 +146,8 @@ __device__ inline void load_slot(int idx, int NL, int& q, int& rg, int& ldst) {
   }
 }
 
-// Partial branch weights of the tile, one per wave column (fixed
-// granularity: the 64 complex columns of a wave), staged in LDS and stored as
-// one run of partials per row.  Per row and part (re, im) the sum runs over
-// the columns 16 + t, t, 32 + t, 48 + t (fused multiply-adds in that order),
-// then over t by an xor butterfly (8, 4, 2, 1), then re + im: the same order
-// in both variants.
-// Lane j of a 32-lane half holds columns t and 16 + t (j = t < 16) or 32 + t
-// and 48 + t (j = 16 + t), both parts; swapping 16-lane rows between the two
-// parts gives every lane one part's four columns (lanes t the real parts,
-// 16 + t the imaginary ones), and after a rotate-add by 8 the values repeat
-// with period 8, so that rotations by 4, 2 and 1 meet the butterfly's
-// partners.  Registers and DPP only: no LDS permutes.
-template <int R>
-__device__ inline float add_ror(float s) {
-  return s + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x120 + R, 0xF, 0xF, true));
-}
-__device__ inline float part_sum(float re0, float im0, float re1, float im1) {
-  const auto p0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(re0), __float_as_uint(im0), false, false);
-  const auto p1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(re1), __float_as_uint(im1), false, false);
-  const float x0 = __uint_as_float(p0[0]), x1 = __uint_as_float(p1[0]);
-  const float x2 = __uint_as_float(p0[1]), x3 = __uint_as_float(p1[1]);
-  float s = __builtin_fmaf(x0, x0, x1 * x1);
-  s = __builtin_fmaf(x2, x2, s);
-  s = __builtin_fmaf(x3, x3, s);
-  s = add_ror<8>(s);
-  s = add_ror<4>(s);
-  s = add_ror<2>(s);
-  s = add_ror<1>(s);
-  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
+// Partial branch weights of the tile (part_sum), one per wave column, staged
+// in LDS and stored as one run of partials per row.
 template <int NWC>
 __device__ inline void store_partials(const floatx16 (&acc)[2][4], float* red, int wave, int wr, int half, int j,
                                       int tid, int m0, int rows, float* qpart, size_t qrow, int q0) {
@@ -491,30 +417,6 @@ MPS_LP_KERNEL(contract_fp16_narrow, f16_t, 1, 1)
 
 // ------------------------------------------------------------ fp16f8 ----
 
-typedef int intx4 __attribute__((ext_vector_type(4)));
-typedef int intx8 __attribute__((ext_vector_type(8)));
-
-// E8M0 scale codes of the FP8 products: 2^-19 on the left-vector operand
-// (the common factor of both corrections), 2^0 on the site tensor's.
-constexpr int kScale8L = 127 - 19;
-constexpr int kScale8B = 127;
-
-// turn (above) for a pair plane's E4M3 codes (groups of 8 bytes) and an E2M3
-// record's codes (dwords 0..2 real, 3..5 imaginary parts; dword 6, the scale,
-// is shared: the maximum is the same).
-__device__ inline intx8 turn_e4m3(intx8 w) {
-  intx8 o;
-#pragma unroll
-  for (int i = 0; i < 8; i += 2) {
-    o[i] = w[i + 1] ^ (int)0x80808080u;
-    o[i + 1] = w[i];
-  }
-  return o;
-}
-__device__ inline intx8 turn_e2m3(intx8 w) {
-  return intx8{w[3] ^ 0x20820820, w[4] ^ 0x08208208, w[5] ^ (int)0x82082082u, w[0], w[1], w[2], w[6], 0};
-}
-
 // Smallest power of two s with amax / s <= 448 (the largest finite E4M3
 // value), exponent clamped to the normal FP32 range; 1 for zero or a
 // non-finite amax (which then shows as a non-finite S downstream).
@@ -654,13 +556,14 @@ __global__ __launch_bounds__(256) void pack_f16f8_kernel(const PackProb* probs, 
       // (at least 2^-108, so that the stored scale code 127 + ke - 19 >= 0;
       // a record that small flushes to zero)
       const int ke = max(e2m3_scale_exp(m), -108);
-      const float inv2 = ldexpf(1.f, -ke);
+      const float inv2 = ldexpf(1.f, -ke - 6);
       // this thread's codes, 4 of 6 bits each: low and high parts, re and im
-      uint32_t c[4] = {0u, 0u, 0u, 0u};
+      uint32_t c[4];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        c[2 * (e >> 2)] |= e2m3_code(lo[e] * inv2) << (6 * (e & 3));
-        c[2 * (e >> 2) + 1] |= e2m3_code(hf[e] * inv2) << (6 * (e & 3));
+      for (int i = 0; i < 2; ++i) {
+        const int e = 4 * i;
+        c[2 * i] = e2m3x4(lo[e] * inv2, lo[e + 1] * inv2, lo[e + 2] * inv2, lo[e + 3] * inv2);
+        c[2 * i + 1] = e2m3x4(hf[e] * inv2, hf[e + 1] * inv2, hf[e + 2] * inv2, hf[e + 3] * inv2);
       }
       // Site record: the 8 real parts' low codes, their high codes, then the
       // same of the imaginary parts; complex 0..3 of the slice from the

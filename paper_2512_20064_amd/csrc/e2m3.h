@@ -18,6 +18,7 @@ constexpr float kE2M3Max = 7.5f;
 // exponent field rebased (127 + E becomes E + 1); a carry out of the
 // mantissa bumps the exponent as it should.  Below 1 the values are the
 // multiples of 1/8 (subnormal codes 0 .. 7; 8 is 1.0).
+// The definition; the kernels use e2m3x4 (lp_ops.h).
 __host__ __device__ inline unsigned e2m3_code(float x) {
   const unsigned u = __builtin_bit_cast(unsigned, x);
   const unsigned sgn = (u >> 26) & 32u;
@@ -37,22 +38,6 @@ __host__ __device__ inline int e2m3_scale_exp(float amax) {
   const float m = frexpf(amax, &E);  // amax = m * 2^E, m in [0.5, 1); 7.5 = 0.9375 * 2^3
   int k = m <= 0.9375f ? E - 3 : E - 2;
   return k < -126 ? -126 : (k > 127 ? 127 : k);
-}
-
-// A whole 32-byte record: codes 0..31 in bytes 0..23, the E8M0 scale code in
-// byte 24, zeros after.
-__device__ inline void e2m3_store_record(unsigned char* dst, const unsigned (&c)[32], unsigned scale_code) {
-  uint32_t w[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int p = 0; p < 32; ++p) {
-    const int bit = 6 * p, word = bit >> 5, off = bit & 31;
-    w[word] |= (c[p] & 63u) << off;
-    if (off > 26) w[word + 1] |= (c[p] & 63u) >> (32 - off);
-  }
-  w[6] = scale_code & 0xFFu;
-  uint4* d = reinterpret_cast<uint4*>(dst);
-  d[0] = make_uint4(w[0], w[1], w[2], w[3]);
-  d[1] = make_uint4(w[4], w[5], w[6], w[7]);
 }
 
 }  // namespace mps

@@ -33,7 +33,7 @@
 // waves per row with the row held in registers (measure_disp_pair_kernel,
 // d <= 4 and chi_r <= 1024), else one wave per row (measure_disp_kernel).
 
-#include "e2m3.h"
+#include "lp_ops.h"
 #include "philox.h"
 #include "sweep.h"
 
@@ -41,9 +41,6 @@
 
 namespace mps {
 namespace {
-
-typedef __bf16 bf16_t;
-typedef _Float16 f16_t;
 
 constexpr int DMAX = 16;
 
@@ -88,13 +85,7 @@ struct SplitWriter {
   // 16-byte store per plane.
   __device__ void put4(int r4, const float2 (&v)[4]) {
     uint32_t h[4], l[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float x = j < 2 ? v[2 * j].x : v[2 * j - 4].y, y = j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y;
-      const T xh = (T)x, yh = (T)y;
-      h[j] = pack2(xh, yh);
-      l[j] = pack2((T)(x - (float)xh), (T)(y - (float)yh));
-    }
+    split4<T>(v, h, l);
     const size_t w = kblk_off(row, 2 * r4, ld) >> 1;
     *reinterpret_cast<uint4*>(hi + w) = make_uint4(h[0], h[1], h[2], h[3]);
     *reinterpret_cast<uint4*>(lo + w) = make_uint4(l[0], l[1], l[2], l[3]);
@@ -106,9 +97,6 @@ struct SplitWriter {
       *reinterpret_cast<uint4*>(hi + w) = make_uint4(0u, 0u, 0u, 0u);
       *reinterpret_cast<uint4*>(lo + w) = make_uint4(0u, 0u, 0u, 0u);
     }
-  }
-  static __device__ uint32_t pack2(T a, T b) {
-    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
   }
 };
 
@@ -128,13 +116,8 @@ struct LWriter<kOutF16> {
   int ld;
   __device__ LWriter(const MeasureProb& a, int r) : hi((uint32_t*)a.Lh), row((size_t)r), ld(a.ld_out) {}
   __device__ void put4(int r4, const float2 (&v)[4]) {
-    uint32_t h[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f16_t xh = (f16_t)(j < 2 ? v[2 * j].x : v[2 * j - 4].y);
-      const f16_t yh = (f16_t)(j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y);
-      h[j] = (uint32_t)__builtin_bit_cast(uint16_t, xh) | ((uint32_t)__builtin_bit_cast(uint16_t, yh) << 16);
-    }
+    uint32_t h[4], l[4];
+    split4<f16_t>(v, h, l);  // (the low parts are dropped)
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r4, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
   }
   __device__ void pad_from(int k0, int sl, int W) {
@@ -155,31 +138,14 @@ struct LWriter<kOutF16F8> {
   int ld;
   __device__ LWriter(const MeasureProb& a, int r)
       : hi((uint32_t*)a.Lh), p8((unsigned char*)a.Ll), row((size_t)r), ld(a.ld_out) {}
-  static __device__ uint32_t pack2(f16_t a, f16_t b) {
-    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-  }
-  // two values -> two codes of the high part and two of the low part
-  static __device__ void codes2(float x, float y, f16_t& xh, f16_t& yh, unsigned& c_hi, unsigned& c_lo) {
-    xh = (f16_t)x;
-    yh = (f16_t)y;
-    const float xf = (float)xh, yf = (float)yh;
-    c_hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(xf * 256.f, yf * 256.f, 0, false) & 0xFFFFu;
-    c_lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32((x - xf) * 524288.f, (y - yf) * 524288.f, 0, false) & 0xFFFFu;
-  }
   // complex r4 .. r4+3: K values 2*r4 .. 2*r4+7, half of a 16-K slice
   __device__ void put4(int r4, const float2 (&v)[4]) {
-    uint32_t h[4];
-    unsigned ch[4], cl[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      f16_t xh, yh;
-      codes2(j < 2 ? v[2 * j].x : v[2 * j - 4].y, j < 2 ? v[2 * j + 1].x : v[2 * j - 3].y, xh, yh, ch[j], cl[j]);
-      h[j] = pack2(xh, yh);
-    }
+    uint32_t h[4], ch[2], cl[2];
+    split4_e4m3(v, h, ch, cl);
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r4, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
     const size_t o = pair_off(row, 2 * r4, ld);
-    *reinterpret_cast<uint2*>(p8 + o) = make_uint2(ch[0] | (ch[1] << 16), ch[2] | (ch[3] << 16));
-    *reinterpret_cast<uint2*>(p8 + o + 16) = make_uint2(cl[0] | (cl[1] << 16), cl[2] | (cl[3] << 16));
+    *reinterpret_cast<uint2*>(p8 + o) = make_uint2(ch[0], ch[1]);
+    *reinterpret_cast<uint2*>(p8 + o + 16) = make_uint2(cl[0], cl[1]);
   }
   __device__ void pad_from(int k0, int sl, int W) {
     for (int k = k0 + 8 * sl; k < ld; k += 8 * W) {
@@ -194,9 +160,8 @@ struct LWriter<kOutF16F8> {
 // fp16f6 writer: the fp16 plane as fp16f8, and per 16-K slice one E2M3
 // record of the 32 values Lh * 2^8 and (x - Lh) * 2^19 (codes 0..7 and 8..15
 // the real parts', 16..23 and 24..31 the imaginary parts') divided by the
-// record's power of two 2^k (E8M0 code 127 + k in byte 24).  A record needs the whole slice, so this writer takes pieces of
-// 8 complex (put8) and the measurement never hands it single values (the
-// displaced measurement forms whole slices for it too).
+// record's power of two 2^k (E8M0 code 127 + k in byte 24).  A record needs
+// the whole slice, so this writer takes pieces of 8 complex (put8).
 template <>
 struct LWriter<kOutF16F6> {
   uint32_t* hi;
@@ -207,35 +172,13 @@ struct LWriter<kOutF16F6> {
       : hi((uint32_t*)a.Lh), p6((unsigned char*)a.Ll), row((size_t)r), ld(a.ld_out) {}
   // complex r8 .. r8+7: the 16 K values 2*r8 .. 2*r8+15 of one slice
   __device__ void put8(int r8, const float2 (&v)[8]) {
-    float hv[16], lv[16];
-    uint32_t h[8];
-    float m = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      // word j of the plane: re 0 1, re 2 3, im 0 1, im 2 3, then the same of complex 4 .. 7
-      const int e = 4 * (j >> 2) + 2 * (j & 1);
-      const float x = j & 2 ? v[e].y : v[e].x, y = j & 2 ? v[e + 1].y : v[e + 1].x;
-      const f16_t xh = (f16_t)x, yh = (f16_t)y;
-      h[j] = (uint32_t)__builtin_bit_cast(uint16_t, xh) | ((uint32_t)__builtin_bit_cast(uint16_t, yh) << 16);
-      const float xf = (float)xh, yf = (float)yh;
-      const int t = (j & 2 ? 8 : 0) + e;  // 0..7 the real parts, 8..15 the imaginary ones
-      hv[t] = xf * 256.f;
-      hv[t + 1] = yf * 256.f;
-      lv[t] = (x - xf) * 524288.f;
-      lv[t + 1] = (y - yf) * 524288.f;
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(hv[t]), fabsf(hv[t + 1])), fmaxf(fabsf(lv[t]), fabsf(lv[t + 1]))));
-    }
+    uint32_t h[8], w[8];
+    split8_e2m3(v, h, w);
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r8, ld) >> 1)) = make_uint4(h[0], h[1], h[2], h[3]);
     *reinterpret_cast<uint4*>(hi + (kblk_off(row, 2 * r8 + 8, ld) >> 1)) = make_uint4(h[4], h[5], h[6], h[7]);
-    const int k = e2m3_scale_exp(m);
-    const float inv = ldexpf(1.f, -k);
-    unsigned c[32];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      c[(e & 7) + 2 * (e & 8)] = e2m3_code(hv[e] * inv);
-      c[(e & 7) + 2 * (e & 8) + 8] = e2m3_code(lv[e] * inv);
-    }
-    e2m3_store_record(p6 + pair_off(row, 2 * r8, ld), c, (unsigned)(127 + k));
+    uint4* d = reinterpret_cast<uint4*>(p6 + pair_off(row, 2 * r8, ld));
+    d[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    d[1] = make_uint4(w[4], w[5], w[6], w[7]);
   }
   __device__ void pad_from(int k0, int sl, int W) {
     for (int k = k0 + 16 * sl; k < ld; k += 16 * W) {

@@ -240,6 +240,48 @@ struct Tables {
   }
 };
 
+// Medium-bond chains (sweep_mid.hip): largest packed size of a call's chains.
+constexpr size_t kMidPackedBytes = size_t(1) << 30;
+
+// Whether every site of a chain fits the persistent medium-bond kernel.
+bool mid_eligible(const Chain& c) {
+  for (int k = 0; k < c.M; ++k)
+    if (mps::mid_groups(c.d[k], c.chi[k + 1]) > mps::kMidGroups) return false;
+  return c.sh.chimax <= mps::kMidChi;
+}
+// Kernel variant of an eligible chain: 0 (up to 4 groups: 4 waves of one group
+// each), 1 (up to 8: 8 waves) or 2 (up to 16: 8 waves of up to two).
+int mid_variant(const Chain& c) {
+  int v = 0;
+  for (int k = 0; k < c.M; ++k) {
+    const int g = mps::mid_groups(c.d[k], c.chi[k + 1]);
+    v = std::max(v, g > 8 ? 2 : g > 4 || c.d[k] > 8 ? 1 : 0);
+  }
+  return v;
+}
+// One packed site: plane bytes, column scales, column maxima of row blocks.
+struct MidPack {
+  size_t plane, cs, part, bytes;
+};
+MidPack mid_pack(int K, int d, int chi_r, int precision) {
+  const int CP = mps::lp_pad_cols(chi_r, mps::kTileNarrow);
+  MidPack m{};
+  m.plane = align_up(((size_t)d * CP + 255) / 256 * 256 * mps::lp_pad_k(K) * 2);
+  m.cs = col_scaled(precision) ? align_up((size_t)d * CP * sizeof(float)) : 0;
+  m.part = col_scaled(precision) ? align_up((size_t)mps::colmax_blocks(K) * d * CP * sizeof(float)) : 0;
+  m.bytes = 2 * m.plane + m.cs + m.part;
+  return m;
+}
+size_t mid_bytes(const Chain& c, int precision) {
+  size_t b = 0;
+  for (int k = 0; k < c.M; ++k) b += mid_pack(c.chi[k], c.d[k], c.chi[k + 1], precision).bytes;
+  return b;
+}
+size_t mid_table_bytes(const Chain& c) {
+  return (size_t)c.M * (sizeof(mps::MidSite) + sizeof(mps::PackProb) + 2 * sizeof(int)) + sizeof(mps::MidChain) +
+         2 * sizeof(int) + 4 * 256 + 3072;
+}
+
 struct Step {
   int nprob = 0;
   // contraction problems of the step by tile variant (wide, narrow): count,
@@ -541,8 +583,53 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       return fail(MPS_ENOMEM, "scratch for %lld-sample chunks (%zu B) plus site staging (%zu B) exceeds "
                   "%s (%lld B)", (long long)nc, scratch_for(nc, nullptr), stage_need, cap_name, (long long)cap);
   }
+  // ---- chains for the persistent medium-bond kernel ----
+  // Split forms, device-resident complex64 sites, no displacement,
+  // every site within the kernel's registers and LDS (mid_eligible): the site
+  // tensors are packed once for the call and the whole chain goes through all
+  // its sites in one launch per chunk (sweep_mid.hip), with the bits of the
+  // per-site launches.  The chunk is planned as for the per-site launches; a
+  // capped call takes this path only if every chain can and the packed sites
+  // fit, so that what fits under a cap does not change.
+  std::vector<Chain> mids, big_chains;
+  if (split && o.fused_small == 0 && !any_staged && !(single && o.displace)) {
+    size_t packed = 0;
+    for (const Chain& c : chains) {
+      const size_t bytes = mid_eligible(c) ? mid_bytes(c, o.precision) : 0;
+      if (bytes && packed + bytes <= kMidPackedBytes) {
+        packed += bytes;
+        mids.push_back(c);
+      } else {
+        big_chains.push_back(c);
+      }
+    }
+    if (!mids.empty() && cap > 0 &&
+        (!big_chains.empty() || (int64_t)(packed + align_up(table_for(1)) + 1024) > cap)) {
+      mids.clear();
+    } else if (!mids.empty()) {
+      chains.swap(big_chains);
+      B = (int)chains.size();
+      Mmax = 0;
+      for (const Chain& c : chains) Mmax = std::max(Mmax, c.M);
+    }
+  }
+  const int nmid = (int)mids.size();
+  double mid_flops_per_row = 0.0, mid_meas_bytes_per_row = 0.0;
+  int Mmid = 0;
+  size_t mid_data = 0, mid_tables = 0;
+  for (const Chain& c : mids) {
+    mid_data += mid_bytes(c, o.precision);
+    mid_tables += mid_table_bytes(c);
+    Mmid = std::max(Mmid, c.M);
+    for (int k = 0; k < c.M; ++k) {
+      mid_flops_per_row += 8.0 * c.chi[k] * c.d[k] * c.chi[k + 1];
+      mid_meas_bytes_per_row += mps::mid_groups(c.d[k], c.chi[k + 1]) * 4.0 + 2.0 * c.chi[k + 1] * 8 + 4 + 16;
+    }
+  }
+  small_bytes += mid_tables;
   std::vector<ChainBufs> bufs(B);
-  const size_t total = scratch_for(nc, &bufs);
+  const size_t mid_at = scratch_for(nc, &bufs);
+  const size_t total = mid_at + mid_data;
   const int64_t nchunks = (N + nc - 1) / nc;
   const int64_t nstate = nstate_for(nc);
   const size_t table_bytes = table_for(nstate);
@@ -745,6 +832,68 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
     small_off = tab.put(sc);
     small_start_off = tab.put(starts);
   }
+  // medium-bond chains: packing problems of every site, site tables, 32
+  // samples per workgroup; one launch per kernel variant, the longest chains
+  // first
+  struct MidLaunch {
+    size_t chains = 0, starts = 0;
+    int n = 0, items = 0, chimax = 1;
+  } mid_launch[3];
+  size_t mid_pk = 0, mid_blk = 0, mid_cm = 0;
+  int mid_sites = 0, mid_blk_total = 0, mid_cm_total = 0;
+  if (nmid) {
+    std::stable_sort(mids.begin(), mids.end(), [](const Chain& a, const Chain& b) { return a.M > b.M; });
+    std::vector<mps::PackProb> pk;
+    std::vector<int> blks(1, 0), cms(1, 0);
+    size_t off = mid_at;
+    for (int w = 0; w < 3; ++w) {
+      MidLaunch& ml = mid_launch[w];
+      std::vector<mps::MidChain> mc;
+      std::vector<int> starts(1, 0);
+      for (const Chain& c : mids) {
+        if (mid_variant(c) != w) continue;
+        std::vector<mps::MidSite> ms(c.M);
+        for (int k = 0; k < c.M; ++k) {
+          const int K = c.chi[k], dk = c.d[k], chr = c.chi[k + 1];
+          const int CP = mps::lp_pad_cols(chr, mps::kTileNarrow), Kp = mps::lp_pad_k(K);
+          const MidPack m = mid_pack(K, dk, chr, o.precision);
+          char* const q = base + off;
+          float* const cs = m.cs ? (float*)(q + 2 * m.plane) : nullptr;
+          ms[k] = mps::MidSite{q, q + m.plane, cs, K, Kp, dk, chr, CP, 0};
+          pk.push_back(mps::PackProb{(const float2*)c.tensors[k], q, q + m.plane, K, dk, chr, CP, Kp, cs,
+                                     cs ? (float*)((char*)cs + m.cs) : nullptr});
+          blks.push_back(blks.back() + (CP / 64) * (Kp / 64) * dk);
+          cms.push_back(cms.back() + mps::colmax_blocks(K) * (CP / 64) * dk);
+          off += m.bytes;
+        }
+        mps::MidChain q{};
+        q.sites = (const mps::MidSite*)(dtab + tab.put(ms));
+        q.M = c.M;
+        q.mps_id = c.mps_id;
+        q.outcomes = c.outcomes;
+        q.logp = c.logp;
+        if (single && o.emit_n > 0) {
+          q.emit_n = o.emit_n;
+          q.emit_dmax = o.emit_dmax;
+          q.emit_probs = o.emit_probs;
+          q.emit_u = o.emit_u;
+        }
+        mc.push_back(q);
+        starts.push_back(starts.back() + (int)((nc + mps::kMidRows - 1) / mps::kMidRows));
+        ml.chimax = std::max(ml.chimax, c.sh.chimax);
+      }
+      ml.n = (int)mc.size();
+      ml.items = starts.back();
+      ml.chains = tab.put(mc);
+      ml.starts = tab.put(starts);
+    }
+    mid_sites = (int)pk.size();
+    mid_blk_total = blks.back();
+    mid_cm_total = cms.back();
+    mid_pk = tab.put(pk);
+    mid_blk = tab.put(blks);
+    mid_cm = tab.put(cms);
+  }
   if (tab.blob.size() > table_bytes) return fail(MPS_EINVAL, "internal: problem tables exceed their reservation");
   if ((e = hipMemcpyAsync(dtab, tab.blob.data(), tab.blob.size(), hipMemcpyHostToDevice, stream)) != hipSuccess)
     return hip_fail(e, "hipMemcpyAsync (problem tables)");
@@ -757,14 +906,15 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
   // Timing events per site: pack, contraction, measurement, copy, expansion
   // (begin, end); a pair is summed once its end has been recorded and waited.
   constexpr int EV = 10;
-  const size_t nev = prof ? (size_t)EV * Mmax + 2 : 0;  // + the small-bond launch (begin, end)
+  // + begin and end of the small-bond launch, the medium-bond launches, their packing
+  const size_t nev = prof ? (size_t)EV * Mmax + 6 : 0;
   while (h->events.size() < nev) {
     hipEvent_t ev;
     if ((e = hipEventCreate(&ev)) != hipSuccess) return hip_fail(e, "hipEventCreate");
     h->events.push_back(ev);
   }
   std::vector<unsigned> rec(prof ? Mmax : 0, 0u);
-  bool rec_small = false;
+  bool rec_fused[3] = {false, false, false};
   auto mark = [&](int k, int which, hipStream_t s) -> int {
     if (!prof) return MPS_OK;
     if (which & 1) rec[k] |= 1u << (which >> 1);
@@ -859,21 +1009,47 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
     MPS_HIP(hipEventRecord(h->ev_expand[k & 1], stream), "hipEventRecord");
     return MPS_OK;
   };
+  // Event before (end = 0) or after (1) the launches of kind i outside the
+  // per-site ones: 0 small-bond, 1 medium-bond, 2 its packing.
+  auto mark_fused = [&](int i, int end) -> int {
+    if (!prof) return MPS_OK;
+    if (end) rec_fused[i] = true;
+    MPS_HIP(hipEventRecord(h->events[EV * Mmax + 2 * i + end], stream), "hipEventRecord");
+    return MPS_OK;
+  };
   auto run_small = [&](const mps::ChunkArgs* ch) -> int {
-    if (prof) MPS_HIP(hipEventRecord(h->events[EV * Mmax], stream), "hipEventRecord");
+    MPS_TRY(mark_fused(0, 0));
     MPS_HIP(mps::launch_sweep_small((const mps::SmallChain*)tp(small_off), (const int*)tp(small_start_off), nsmall,
                                     small_items, ch, seed, nflag, stream),
             "small-bond sweep launch");
-    if (prof) {
-      MPS_HIP(hipEventRecord(h->events[EV * Mmax + 1], stream), "hipEventRecord");
-      rec_small = true;
-    }
-    return MPS_OK;
+    return mark_fused(0, 1);
+  };
+  // Once per call: every site of the medium-bond chains into operand form.
+  auto run_mid_pack = [&]() -> int {
+    MPS_TRY(mark_fused(2, 0));
+    if (mps::is_f8f6(form))
+      MPS_HIP(mps::launch_colscale((const mps::PackProb*)tp(mid_pk), (const int*)tp(mid_cm), mid_sites, mid_cm_total,
+                                   stream),
+              "column-scale launch");
+    MPS_HIP(mps::launch_pack_lp(form, (const mps::PackProb*)tp(mid_pk), (const int*)tp(mid_blk), mid_sites,
+                                mid_blk_total, stream),
+            "pack launch");
+    return mark_fused(2, 1);
+  };
+  auto run_mid = [&](const mps::ChunkArgs* ch) -> int {
+    MPS_TRY(mark_fused(1, 0));
+    for (int w = 2; w >= 0; --w)
+      MPS_HIP(mps::launch_sweep_mid(form, 4 << w, (const mps::MidChain*)tp(mid_launch[w].chains),
+                                    (const int*)tp(mid_launch[w].starts), mid_launch[w].n, mid_launch[w].items,
+                                    mid_launch[w].chimax, ch, seed, nflag, stream),
+              "medium-bond sweep launch");
+    return mark_fused(1, 1);
   };
   // All launches of one chunk (chunks-outer order), grids sized for grid_rows.
   auto launch_chunk = [&](int grid_rows) -> int {
     const mps::ChunkArgs* cur = chunk_tab;
     if (nsmall) MPS_TRY(run_small(cur));
+    if (nmid) MPS_TRY(run_mid(cur));
     MPS_TRY(run_init(0, cur, grid_rows));
     for (int k = 0; k < Mmax; ++k) {
       MPS_TRY(run_pack(k));
@@ -909,11 +1085,14 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       }
       rec[k] = 0;
     }
-    if (rec_small) {
+    double* fdst[3] = {&st.fused_ms, &st.contract_ms, &st.pack_ms};
+    for (int i = 0; i < 3; ++i) {
+      if (!rec_fused[i]) continue;
       float ms = 0.f;
-      MPS_HIP(hipEventElapsedTime(&ms, h->events[EV * Mmax], h->events[EV * Mmax + 1]), "hipEventElapsedTime");
-      st.fused_ms += ms;
-      rec_small = false;
+      MPS_HIP(hipEventElapsedTime(&ms, h->events[EV * Mmax + 2 * i], h->events[EV * Mmax + 2 * i + 1]),
+              "hipEventElapsedTime");
+      *fdst[i] += ms;
+      rec_fused[i] = false;
     }
     return MPS_OK;
   };
@@ -947,6 +1126,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       }
     }
   } else {
+    if (nmid && (rc = run_mid_pack())) return rc;
+    st.pack_launches += nmid ? 1 : 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     if (use_graph) {
@@ -983,6 +1164,11 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
         st.fused_launches++;
         st.fused_flops += small_flops_per_row * ch.rows;
       }
+      // the medium-bond kernel's site steps beyond those of the per-site launches
+      st.contract_launches += std::max(0, Mmid - Mmax);
+      st.measure_launches += std::max(0, Mmid - Mmax);
+      st.contract_flops += mid_flops_per_row * ch.rows;
+      st.measure_bytes += mid_meas_bytes_per_row * ch.rows;
       rc = accumulate();
     }
     if (use_graph) {

@@ -213,6 +213,45 @@ struct SmallChain {
 hipError_t launch_sweep_small(const SmallChain* chains, const int* item_start, int nchain, int items,
                               const ChunkArgs* ch, uint64_t seed, int* nflag, hipStream_t s);
 
+// Persistent medium-bond sweep (the split forms): chains whose sites all
+// have at most kMidGroups groups of 64 complex columns (d * ceil(chi_r / 64))
+// and bonds <= kMidChi, 32 samples per workgroup.
+constexpr int kMidRows = 32;
+constexpr int kMidGroups = 16;
+constexpr int kMidChi = 256;
+__host__ __device__ inline int mid_groups(int d, int chi_r) { return d * (lp_pad_cols(chi_r, kTileNarrow) / 64); }
+// LDS of a workgroup: the operand planes of 32 left vectors, 32 rows of a
+// branch, 2 complex apart so that 16-byte accesses down the rows spread over
+// the banks, and a dump slot per lane.
+__host__ __device__ inline int mid_row_pitch(int chimax) { return (chimax + 1) / 2 * 2 + 2; }
+__host__ __device__ inline size_t mid_lds_bytes(int chimax) {
+  return (size_t)2 * (lp_pad_k(chimax) >> 4) * 1024 + (size_t)kMidRows * mid_row_pitch(chimax) * 8 + 64 * 8;
+}
+
+struct MidSite {
+  const void* Bh;   // packed site tensor (64-column padding)
+  const void* Bl;
+  const float* cs;  // kFp16F8, kFp16F6: column scales
+  int K, Kp, d, chi_r, CP;
+  int pad_;
+};
+struct MidChain {
+  const MidSite* sites;  // [M]
+  int M;
+  int emit_dmax;
+  uint64_t mps_id;
+  int32_t* outcomes;     // as in SmallChain
+  double* logp;
+  int64_t emit_n;
+  double* emit_probs;
+  double* emit_u;
+};
+// groups: 4, 8 or 16, at least the chains' mid_groups (4 also asks for d <= 8);
+// chimax: the largest bond of the chains; items and item_start as in
+// launch_sweep_small.
+hipError_t launch_sweep_mid(int form, int groups, const MidChain* chains, const int* item_start, int nchain, int items,
+                            int chimax, const ChunkArgs* ch, uint64_t seed, int* nflag, hipStream_t s);
+
 // Stored site tensor (device memory) -> complex64 site tensor.
 struct DecompressProb {
   const void* src;

@@ -41,3 +41,66 @@ def test_small_bond_kernel_edges(case):
     _check(t, s, N, first, EPS_FP32)
     assert s.stats.fused_launches == 1 and s.stats.contract_launches == 0
     s.close()
+
+
+# Medium-bond kernel: 4, 5, 8, 9 and 16 groups of 64 columns, bonds that are no
+# multiple of 8, 16 or 64, more branches than a 4-wave workgroup has lanes for,
+# sample counts around a workgroup's 32 rows, chains around a block of sites.
+MID = [
+    # (d_k, chi_k, N, first sample)
+    ([4] * 9, [1, 4, 16, 64, 64, 64, 64, 16, 4, 1], 33, 0),
+    ([2] * 8, [1, 2, 4, 8, 16, 32, 64, 65, 40], 31, 7),
+    ([4, 4, 4, 3, 5, 4, 2], [1, 4, 16, 61, 97, 100, 50, 25], 70, 0),
+    ([4] * 7, [1, 4, 16, 64, 128, 127, 33, 9], 64, 1 << 33),
+    ([4] * 6, [1, 4, 16, 64, 256, 250, 63], 40, 0),
+    ([10, 9, 3, 2], [1, 10, 60, 41, 21], 20, 0),
+    ([16, 16, 2] + [1] * 15, [1, 16, 33, 40] + [40] * 15, 1, 3),
+]
+
+
+@pytest.mark.parametrize("form", ["fp16f6", "fp16f8", "bf16x3", "fp16x3"])
+@pytest.mark.parametrize("case", range(len(MID)))
+def test_medium_bond_kernel_edges(form, case):
+    """The persistent kernel gives the bits of the per-site launches, and both
+    agree with the oracle."""
+    from paper_2512_20064_amd import mps
+    from tests.parity_util import EPS_LOWP, upload
+    d, chi, N, first = MID[case]
+    print(f"[gpu-case] medium-bond edges {form} {case}: M={len(d)} N={N}", flush=True)
+    t = synth.to_c64(synth.random_mps(61 + case, d, chi))
+    a = mps.Sampler(0, precision=form)
+    b = mps.Sampler(0, precision=form, fused_small=False)
+    dev = upload(t)
+    ra = a.sample(dev, N, 77, n_offset=first, emit_n=N)
+    rb = b.sample(dev, N, 77, n_offset=first, emit_n=N)
+    torch.cuda.synchronize()
+    # packed in one launch for the call by the persistent kernel, in one per site otherwise
+    assert a.stats.pack_launches == 1 and a.stats.contract_launches == len(d)
+    assert b.stats.pack_launches == len(d) and b.stats.contract_launches == len(d)
+    for key in ("outcomes", "logp", "u"):
+        assert torch.equal(ra[key], rb[key]), key
+    assert torch.equal(torch.nan_to_num(ra["probs"]), torch.nan_to_num(rb["probs"]))
+    _check(t, a, N, first, EPS_LOWP)
+    a.close()
+    b.close()
+
+
+def test_medium_bond_kernel_batch_and_chunks():
+    """Chains of every kernel variant in one batched call with a ragged last
+    chunk, against one call per chain on the per-site launches."""
+    from paper_2512_20064_amd import mps
+    from tests.parity_util import upload
+    print("[gpu-case] medium-bond batch", flush=True)
+    specs = [([4] * 5, 16), ([4] * 9, 64), ([3] * 11, 100), ([4] * 8, 200), ([2] * 14, 300)]
+    chains = [upload(synth.to_c64(synth.random_mps(90 + i, d, synth.ramp_bonds(d, c)))) for i, (d, c) in
+              enumerate(specs)]
+    s = mps.Sampler(0, precision="fp16f6", n_chunk=100)
+    outs = s.sample_batch(chains, 333, 5)
+    torch.cuda.synchronize()
+    for i, (o, lp) in enumerate(outs):
+        one = mps.Sampler(0, precision="fp16f6", mps_id=i, fused_small=i == 0)
+        r = one.sample(chains[i], 333, 5)
+        torch.cuda.synchronize()
+        assert torch.equal(o, r["outcomes"]) and torch.equal(lp, r["logp"]), i
+        one.close()
+    s.close()
