@@ -55,6 +55,63 @@ struct F32Tile {
   static_assert(BM * BK % NTHR == 0 && BK * BNC % NTHR == 0, "tile loads must divide evenly");
 };
 
+// W and the partial branch weights of a tile (T = BM rows by 64 complex columns).
+template <int BM>
+__device__ inline void f32_epilogue(const ContractProb& a, const floatx16 (&tot)[2][2], float* red, int rows, int m0,
+                                    int branch, int ct, int T) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int wr = (wave >> 1) * 64;
+  const int wc = (wave & 1) * 32;
+  const int half = lane >> 5;
+  const int j = lane & 31;
+  const int c0 = ct * BNC;
+  const int ncols = a.d * a.chi_r;
+  // Epilogue 1: W.  Output lane (j, half) of a 32x32 block holds column j and
+  // rows 8*(v/4) + 4*half + v%4, v = 0..15.
+  float* Wf = reinterpret_cast<float*>(a.W);
+  const size_t wpitch = 2 * (size_t)ncols;
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      const int colc = c0 + wc + cb * 16 + (j >> 1);
+      const size_t fcol = 2 * ((size_t)branch * a.chi_r + c0 + wc + cb * 16) + j;
+      if (colc < a.chi_r) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int gr = m0 + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+          if (gr < rows) Wf[(size_t)gr * wpitch + fcol] = tot[rb][cb][v];
+        }
+      }
+    }
+  }
+
+  // Epilogue 2: partial weight of this (row, branch, 64-column tile).
+  // Columns past chi_r were zero-filled, so they add nothing.  Reduction
+  // order is fixed (the two blocks of a lane, the lanes by xor butterfly,
+  // then the two wave columns of the tile), so the result depends neither on
+  // scheduling nor on the variant (both have the same two wave columns).
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float s = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) s += tot[rb][cb][v] * tot[rb][cb][v];
+#pragma unroll
+      for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 32);
+      if (j == 0) red[(wave & 1) * BM + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3)] = s;
+    }
+  }
+  __syncthreads();
+  if (tid < BM) {
+    const int gr = m0 + tid;
+    if (gr < rows) a.qpart[(size_t)gr * (a.d * T) + branch * T + ct] = red[tid] + red[BM + tid];
+  }
+}
+
 // Waves in a (BM/64) x 2 grid; each owns 64 rows x 32 complex columns, i.e.
 // 2 x 2 output blocks of 32 rows x 16 complex (32 real) columns, so both
 // variants run the same per-wave code and give the same bits.
@@ -194,49 +251,144 @@ __global__ __launch_bounds__(F32Tile<BM>::NTHR, 2) void contract_f32_kernel(cons
     __syncthreads();
   }
 
-  // Epilogue 1: W.  Output lane (j, half) of a 32x32 block holds column j and
-  // rows 8*(v/4) + 4*half + v%4, v = 0..15.
-  float* Wf = reinterpret_cast<float*>(a.W);
-  const size_t wpitch = 2 * (size_t)ncols;
+  f32_epilogue<BM>(a, tot, lds, rows, m0, branch, ct, T);  // the stages are free: the K loop ended on a barrier
+}
+
+// The wide tile with its operands loaded straight into LDS, for problems whose
+// rows are whole 16-byte chunks (K and chi_r even, site tensor 16-byte aligned
+// and under 2 GiB).  A stage (16 complex K) is 128 rows of 128 bytes of left
+// vectors and 16 rows of 512 bytes of the site tensor, both as in memory; two
+// stages, one of them ahead, so that three workgroups share a CU (48 KiB of
+// LDS and 160 registers each).  The loads need no registers, no store phase
+// and no transposition: a lane reads two K values of its row, both
+// parts, as one 16-byte chunk and keeps its part.  The chunks of a row are
+// permuted by (row >> 1) & 7, so that the 16 rows of a read phase lie in
+// distinct banks.  Rows past the chunk, columns past chi_r and K past the
+// tensor are zeros by the descriptors' ranges, or meet zeros.
+//
+// What bounds it: the FP32 matrix cores, 127 of the 137 TFLOP/s that a library
+// product reaches here.  Sweep of 18 sites, 16384 samples, chi = 1024: 36.8 ms
+// against 44.0 for the register-staged kernel below (35.4 without its loads and
+// LDS stores, 39.0 without its second accumulation level); with three stages
+// and two workgroups per CU 38.7, and with the row blocks one after the other,
+// each joining the totals during the other's matrix instructions, 39.5.
+// Sites with odd bonds, or misaligned, take the kernel below.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int DBM = 128;
+constexpr int DST = 2;
+constexpr int DLB = DBM * BK * 8;          // bytes of a left-vector stage
+constexpr int DSTAGE = DLB + BK * BNC * 8;
+constexpr int DIPW = DSTAGE / 1024 / 4;    // 1 KiB load instructions per wave and stage
+static_assert(DIPW == 6, "waits below");
+
+__global__ __launch_bounds__(256, 3) void contract_f32_direct(const ContractProb* probs, const int* tn_start,
+                                                              int nprob, int tn_total, int tiles_m, int per_xcd,
+                                                              int group_m, const ChunkArgs* chp) {
+  __shared__ __attribute__((aligned(16))) char lds[DST * DSTAGE];
+  const int rows = chp->rows;
+  int tm, tng;
+  if (!map_tile(blockIdx.x, tiles_m, tn_total, per_xcd, group_m, tm, tng)) return;
+  const int p = find_problem(tn_start, nprob, tng);
+  const ContractProb a = probs[p];
+  const int tn = tng - tn_start[p];
+  const int T = col_tiles(a.chi_r);
+  const int branch = tn / T;
+  const int ct = tn - branch * T;
+  const int m0 = tm * DBM;
+  const int c0 = ct * BNC;
+  const int ncols = a.d * a.chi_r;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = (wave >> 1) * 64;
+  const int wc = (wave & 1) * 32;
+  const int half = lane >> 5;
+  const int j = lane & 31;
+
+  // Loads: instructions 0..3 of a wave take 8 rows of left vectors each,
+  // 4 and 5 two rows of the site tensor.
+  const int mrows = min(DBM, rows - m0);  // at least 1: the grid covers grid_rows >= rows only
+  const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.L + (size_t)m0 * a.K), (short)0, mrows > 0 ? mrows * a.K * 8 : 0, 0x00020000);
+  const size_t aoff0 = (size_t)branch * a.chi_r + c0;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.A + aoff0), (short)0, (int)(((size_t)a.K * ncols - aoff0) * 8), 0x00020000);
+  unsigned voff[DIPW], vstep[2] = {BK * 8u, (unsigned)(BK * ncols) * 8u};
+  int dst[DIPW];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
+  for (int i = 0; i < DIPW; ++i) {
+    if (i < 4) {
+      const int row = (wave * 4 + i) * 8 + (lane >> 3);
+      voff[i] = (unsigned)(row * a.K * 8 + (((lane & 7) ^ ((row >> 1) & 7)) << 4));
+      dst[i] = (wave * 4 + i) * 1024;
+    } else {
+      const int l = (wave * 2 + i - 4) * 2 + (lane >> 5), c = (lane & 31) * 2;
+      voff[i] = c0 + c < a.chi_r ? (unsigned)(l * ncols + c) * 8u : 0x80000000u;
+      dst[i] = DLB + (wave * 2 + i - 4) * 1024;
+    }
+  }
+  auto issue = [&](int kt) {  // stages in order
+    char* st = lds + (kt % DST) * DSTAGE;
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      const int colc = c0 + wc + cb * 16 + (j >> 1);
-      const size_t fcol = 2 * ((size_t)branch * a.chi_r + c0 + wc + cb * 16) + j;
-      if (colc < a.chi_r) {
+    for (int i = 0; i < DIPW; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 4 ? rl : ra, (__attribute__((address_space(3))) void*)(st + dst[i]),
+                                               16, voff[i], 0, 0, 0);
+      voff[i] += vstep[i >> 2];
+    }
+  };
+
+  floatx16 tot[2][2], blk[2][2];
+  const floatx16 zero = {};
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int gr = m0 + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-          if (gr < rows) Wf[(size_t)gr * wpitch + fcol] = tot[rb][cb][v];
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) tot[rb][cb] = zero;
+
+  const int sw = (j >> 1) & 7;  // rows 32 apart share it
+  const unsigned arow = (unsigned)((wr + j) * 128);
+  const unsigned bcol = (unsigned)(DLB + (2 * wc + (j ^ half)) * 4);
+  const unsigned sgn = (half && !(j & 1)) ? 0x80000000u : 0u;
+  const int nkt = (a.K + BK - 1) / BK;
+  int issued = 0;
+  issue(issued++);
+  for (int kt = 0; kt < nkt; ++kt) {
+    // Stage kt landed (stage kt + 1 may stay in flight) and this wave's LDS
+    // reads of stage kt - 1 are done; after the barrier its buffer is refilled.
+    if (issued > kt + 1) __builtin_amdgcn_s_waitcnt(0x0070 | DIPW);  // vmcnt(DIPW) lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x0070);                         // vmcnt(0) lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+    if (issued < nkt) issue(issued++);
+    const char* st = lds + (kt % DST) * DSTAGE;
+#pragma unroll
+    for (int q = 0; q < BK / 2; ++q) {
+      float av[2][2];
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const floatx4 z = *reinterpret_cast<const floatx4*>(st + arow + rb * 4096 + ((q ^ sw) << 4));
+        av[rb][0] = half ? z[1] : z[0];
+        av[rb][1] = half ? z[3] : z[2];
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int kk = 2 * q + e;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          const float bv = __uint_as_float(
+              *reinterpret_cast<const unsigned*>(st + bcol + kk * (BNC * 8) + cb * 128) ^ sgn);
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb)
+            blk[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[rb][e], bv, kk ? blk[rb][cb] : zero, 0, 0, 0);
         }
       }
     }
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) tot[rb][cb] += blk[rb][cb];
   }
-
-  // Epilogue 2: partial weight of this (row, branch, 64-column tile).
-  // Columns past chi_r were zero-filled, so they add nothing.  Reduction
-  // order is fixed (the two blocks of a lane, the lanes by xor butterfly,
-  // then the two wave columns of the tile), so the result depends neither on
-  // scheduling nor on the variant (both have the same two wave columns).
-  float* red = lds;  // the stages are free: the K loop ended on a barrier
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      float s = 0.f;
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) s += tot[rb][cb][v] * tot[rb][cb][v];
-#pragma unroll
-      for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 32);
-      if (j == 0) red[(wave & 1) * BM + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3)] = s;
-    }
-  }
-  __syncthreads();
-  if (tid < BM) {
-    const int gr = m0 + tid;
-    if (gr < rows) a.qpart[(size_t)gr * (a.d * T) + branch * T + ct] = red[tid] + red[BM + tid];
-  }
+  __syncthreads();  // the stages are reused below
+  f32_epilogue<DBM>(a, tot, reinterpret_cast<float*>(lds), rows, m0, branch, ct, T);
 }
 
 }  // namespace
@@ -255,8 +407,17 @@ hipError_t launch_f32_t(const ContractProb* probs, const int* tn_start, int npro
 }
 }  // namespace
 
-hipError_t launch_contract_f32(int tile, const ContractProb* probs, const int* tn_start, int nprob, int tn_total,
-                               const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
+hipError_t launch_contract_f32(int tile, bool chunked, const ContractProb* probs, const int* tn_start, int nprob,
+                               int tn_total, const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s) {
+  if (tile == kTileWide && chunked) {
+    const int tiles_m = (grid_rows + DBM - 1) / DBM;
+    const long long ntiles = (long long)tiles_m * tn_total;
+    if (ntiles <= 0 || nprob <= 0) return hipSuccess;
+    const int per_xcd = (int)((ntiles + 7) / 8);
+    hipLaunchKernelGGL(contract_f32_direct, dim3(per_xcd * 8), dim3(256), 0, s, probs, tn_start, nprob, tn_total,
+                       tiles_m, per_xcd, group_m, ch);
+    return hipGetLastError();
+  }
   if (tile == kTileNarrow) return launch_f32_t<64>(probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
   return launch_f32_t<128>(probs, tn_start, nprob, tn_total, ch, grid_rows, group_m, s);
 }

@@ -287,6 +287,7 @@ struct Step {
   // contraction problems of the step by tile variant (wide, narrow): count,
   // column tiles over them, and their tables
   int ncp[2] = {0, 0};
+  bool chunked = true;  // FP32: every problem in 16-byte chunks (f32_chunked)
   int tn_tot[2] = {0, 0};
   size_t ctab[2] = {0, 0}, tntab[2] = {0, 0};
   int blk_total = 0;  // packing blocks over all problems of the step
@@ -739,6 +740,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
           mps::ContractProb cp{(const float2*)sat(b, bufs[b].L), site_A(b, k), (float2*)at(bufs[b].W),
                                (float*)at(bufs[b].qpart), K, dk, chr};
           cf[tile].push_back(cp);
+          sp.chunked = sp.chunked && mps::f32_chunked(cp.A, K, dk, chr);
           tns[tile].push_back(tns[tile].back() + dk * mps::col_tiles(chr));
         }
         mps::MeasureProb mp{};
@@ -969,7 +971,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
                                     (const int*)tp(sp.tntab[v]), sp.ncp[v], sp.tn_tot[v], ch, grid_rows, group,
                                     stream);
       else
-        e = mps::launch_contract_f32(v, (const mps::ContractProb*)tp(sp.ctab[v]), (const int*)tp(sp.tntab[v]),
+        e = mps::launch_contract_f32(v, sp.chunked, (const mps::ContractProb*)tp(sp.ctab[v]), (const int*)tp(sp.tntab[v]),
                                      sp.ncp[v], sp.tn_tot[v], ch, grid_rows, group, stream);
       if (e != hipSuccess) return hip_fail(e, "contraction launch");
     }
@@ -1612,7 +1614,8 @@ int mps_autotune_tiles(mps_handle h, int32_t B, const mps_chain* chains_in, int6
       auto launch = [&]() {
         return lowp ? mps::launch_contract_lp(form, v, (const mps::ContractLpProb*)tabd, (const int*)(tabd + 1024), 1,
                                               tn_total, (const mps::ChunkArgs*)(tabd + 1088), (int)rows, group, stream)
-                    : mps::launch_contract_f32(v, (const mps::ContractProb*)tabd, (const int*)(tabd + 1024), 1,
+                    : mps::launch_contract_f32(v, mps::f32_chunked(kv.second, K, dk, chr),
+                                               (const mps::ContractProb*)tabd, (const int*)(tabd + 1024), 1,
                                                tn_total, (const mps::ChunkArgs*)(tabd + 1088), (int)rows, group,
                                                stream);
       };

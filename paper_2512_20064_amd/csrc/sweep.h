@@ -268,8 +268,14 @@ hipError_t launch_zero_int(int* p, int n, hipStream_t s);
 hipError_t launch_fill_noise(void* p, size_t n, int kind, unsigned seed, hipStream_t s);
 // form: 0 = FP32 path, kBf16x3, kFp16
 hipError_t launch_init(int form, const InitProb* probs, int nprob, const ChunkArgs* ch, int grid_rows, hipStream_t s);
-hipError_t launch_contract_f32(int tile, const ContractProb* probs, const int* tn_start, int nprob, int tn_total,
-                               const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s);
+// chunked: every problem satisfies f32_chunked (the wide tile then loads its
+// operands straight into LDS).
+hipError_t launch_contract_f32(int tile, bool chunked, const ContractProb* probs, const int* tn_start, int nprob,
+                               int tn_total, const ChunkArgs* ch, int grid_rows, int group_m, hipStream_t s);
+inline bool f32_chunked(const void* A, int K, int d, int chi_r) {
+  return K % 2 == 0 && chi_r % 2 == 0 && (uintptr_t)A % 16 == 0 &&
+         ((uint64_t)K + kBK) * d * chi_r * 8 < ((uint64_t)1 << 31);
+}
 hipError_t launch_pack_lp(int form, const PackProb* probs, const int* blk_start, int nprob, int blk_total,
                           hipStream_t s);
 // kFp16F8, kFp16F6: column maxima of the problems' site tensors per row block (before

@@ -104,3 +104,36 @@ def test_medium_bond_kernel_batch_and_chunks():
         assert torch.equal(o, r["outcomes"]) and torch.equal(lp, r["logp"]), i
         one.close()
     s.close()
+
+
+@pytest.mark.parametrize("d,chi,N", [
+    ([4] * 8, [1, 4, 16, 64, 130, 66, 34, 10, 4], 129),   # column and K tails of 2
+    ([2, 4, 4, 6, 4, 2], [1, 2, 8, 32, 192, 62, 32], 127),
+    ([4] * 6, [1, 4, 16, 63, 128, 65, 17], 200),           # odd bonds beside even ones
+])
+def test_fp32_direct_tile_edges(d, chi, N):
+    """FP32 wide tile loaded straight into LDS: the bits of the register-staged
+    narrow tile, also where a site starts 8 bytes off a 16-byte boundary (the
+    register-staged wide tile), and the oracle."""
+    from paper_2512_20064_amd import mps
+    from tests.parity_util import EPS_FP32, upload
+    print(f"[gpu-case] fp32 direct tile chi={chi} N={N}", flush=True)
+    t = synth.to_c64(synth.random_mps(81, d, chi))
+    s = mps.Sampler(0, fused_small=False)
+    _check(t, s, N, 0, EPS_FP32)
+    dev = upload(t)
+    wide = s.sample(dev, N, 77)
+    off = []
+    for x in dev:
+        buf = torch.empty(x.numel() + 1, dtype=torch.complex64, device="cuda")
+        buf[1:] = x.reshape(-1)
+        off.append(buf[1:].view(x.shape))
+    assert all(x.data_ptr() % 16 == 8 for x in off)
+    shifted = s.sample(off, N, 77)
+    s.set_tiles([dict(chi_l=a, d=b, chi_r=c, tile=mps.MPS_TILE_NARROW, rows=N) for a, b, c in
+                 {tuple(x.shape) for x in dev}])
+    narrow = s.sample(dev, N, 77)
+    torch.cuda.synchronize()
+    for r in (shifted, narrow):
+        assert torch.equal(r["outcomes"], wide["outcomes"]) and torch.equal(r["logp"], wide["logp"])
+    s.close()
