@@ -390,100 +390,189 @@ __global__ __launch_bounds__(256) void measure_disp_kernel(const MeasureProb* pr
   out.pad_from(2 * PC * nq, lane, 64);
 }
 
+// D(mu) for d <= 4, entry t of the lane t < d * d: the terms of
+// displacement_entry with the powers mu^a (-mu^*)^b formed once each, by lane
+// 4 a + b, and shared through LDS (pw: 16 complex), and the constants
+// sqrt(i! j!) / (k! (i-k)! (j-k)!) tabled.  The same operations in the same
+// order, about a sixth of the instructions.
+constexpr double kSqrt2 = 1.4142135623730951, kSqrt6 = 2.449489742783178, kSqrt12 = 3.4641016151377544;
+__constant__ double kDispC[4][4][4] = {
+    {{1.0}, {1.0}, {kSqrt2 / 2.0}, {kSqrt6 / 6.0}},
+    {{1.0}, {1.0, 1.0}, {kSqrt2 / 2.0, kSqrt2}, {kSqrt6 / 6.0, kSqrt6 / 2.0}},
+    {{kSqrt2 / 2.0}, {kSqrt2 / 2.0, kSqrt2}, {2.0 / 4.0, 2.0, 2.0 / 2.0}, {kSqrt12 / 12.0, kSqrt12 / 2.0, kSqrt12 / 2.0}},
+    {{kSqrt6 / 6.0}, {kSqrt6 / 6.0, kSqrt6 / 2.0}, {kSqrt12 / 12.0, kSqrt12 / 2.0, kSqrt12 / 2.0},
+     {6.0 / 36.0, 6.0 / 4.0, 6.0 / 2.0, 6.0 / 6.0}}};
+__device__ inline void displacement4(double mr, double mi, int d, int lane, double2* pw, float2* D) {
+  if (lane < 16) {
+    double pr = 1.0, pi = 0.0;
+    const int ea = lane >> 2, eb = lane & 3;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const double nr = pr * mr - pi * mi, ni = pr * mi + pi * mr;
+      if (t < ea) {
+        pr = nr;
+        pi = ni;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const double nr = pr * (-mr) - pi * mi, ni = pr * mi + pi * (-mr);
+      if (t < eb) {
+        pr = nr;
+        pi = ni;
+      }
+    }
+    pw[lane] = make_double2(pr, pi);
+  }
+  __builtin_amdgcn_wave_barrier();  // one wave: its LDS operations are in order
+  if (lane < d * d) {
+    const int i = lane / d, j = lane - i * d;
+    double sr = 0.0, si = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k <= min(i, j)) {
+        const double2 q = pw[4 * (i - k) + j - k];
+        const double c = kDispC[i][j][k];
+        sr += c * q.x;
+        si += c * q.y;
+      }
+    }
+    const double g = exp(-0.5 * (mr * mr + mi * mi));
+    D[lane] = make_float2((float)(g * sr), (float)(g * si));
+  }
+}
+
+// v + (v of lane ^ X), X = 32 and 16 by row swaps; then, the values repeating
+// with period X, rotations of 16-lane rows by 8, 4, 2, 1 meet lane ^ X: the
+// butterfly's additions without LDS permutes.
+template <int X>
+__device__ inline double add_xor(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+  if constexpr (X >= 16) {
+    const auto l = X == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                           : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = X == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                           : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __builtin_bit_cast(double, (uint64_t)h[0] << 32 | l[0]) +
+           __builtin_bit_cast(double, (uint64_t)h[1] << 32 | l[1]);
+  } else {
+    const uint32_t l = __builtin_amdgcn_update_dpp(0, lo, 0x120 + X, 0xF, 0xF, true);
+    const uint32_t h = __builtin_amdgcn_update_dpp(0, hi, 0x120 + X, 0xF, 0xF, true);
+    return v + __builtin_bit_cast(double, (uint64_t)h << 32 | l);
+  }
+}
+
+// W' of one column and branch: sum_j g_j w_j, in order of j.
+template <int ND>
+__device__ inline float2 displaced(const float2 (&g)[ND], const float2 (&w)[ND][8], int e) {
+  float xr = 0.f, xi = 0.f;
+#pragma unroll
+  for (int jj = 0; jj < ND; ++jj) {
+    xr += __builtin_fmaf(g[jj].x, w[jj][e].x, -(g[jj].y * w[jj][e].y));
+    xi += __builtin_fmaf(g[jj].y, w[jj][e].x, g[jj].x * w[jj][e].y);
+  }
+  return make_float2(xr, xi);
+}
+
 // The displaced measurement for d <= 4 and chi_r <= 1024 with W read once:
 // two waves per sample (a workgroup of four waves takes two samples), lane
 // l of the sample's wave h holding the 8 consecutive complex from
 // 512 h + 8 l of every branch in registers from the weights pass to the
-// gather.  Each wave's FP32 lane sums are added in FP64 by the fixed
-// butterfly, then the two waves' sums (first + second) in LDS; one lane per
-// sample makes the decision.  With chi_r a multiple of 8 every piece is
-// whole and 16-byte aligned, and a lane whose piece starts past chi_r reads
-// the row's last piece instead (in bounds; masked out of the weights and
-// not written), so the loads carry no lane-dependent branch.
-template <int OUT>
-__global__ __launch_bounds__(256) void measure_disp_pair_kernel(const MeasureProb* probs, const ChunkArgs* chp,
-                                                                uint64_t seed, int* nflag) {
-  constexpr int DM = 4;
-  __shared__ float2 Dsh[2][DM * DM];
-  __shared__ double qsh[4][DM];
+// gather, D(mu) in registers beside them (ND = d).  Each wave's FP32 lane sums
+// are added in FP64 by the fixed butterfly, then the two waves' sums (first +
+// second) in LDS; one lane per sample makes the decision, with the uniform
+// that the sample's second wave drew while the first built D.  With chi_r a
+// multiple of 8 every piece is whole and 16-byte aligned, and a lane whose
+// piece starts past chi_r reads the row's last piece instead (in bounds;
+// masked out of the weights and not written), so the loads carry no
+// lane-dependent branch.
+//
+// What bounds it: instructions (about 1400 a wave), then HBM (W is read once).
+// Sweep of 18 sites, 32768 samples, d = 4, chi = 1024, fp16f6: 18.1 ms against
+// 19.4 with D read from LDS in loops over d, LDS permutes in the butterfly and
+// every entry of D formed on its own (ablations of the latter: 15.2 without the
+// weights pass, 17.5 without the permutes, 18.3 without D).
+template <int OUT, int ND>
+__device__ inline void measure_disp_pair(const MeasureProb& a, const ChunkArgs& ch, uint64_t seed, int* nflag) {
+  __shared__ __attribute__((aligned(16))) float2 Dsh[2][16];
+  __shared__ double2 pw[2][16];
+  __shared__ double qsh[4][4];
+  __shared__ double u_sh[2];
   __shared__ int s_sh[2];
   __shared__ float scale_sh[2];
-  const ChunkArgs ch = *chp;
-  const MeasureProb a = probs[blockIdx.y];
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
   const int rl = wv >> 1, h = wv & 1;
   const int row = blockIdx.x * 2 + rl;
-  if (blockIdx.x * 2 >= ch.rows) return;  // the whole workgroup
-  const bool live = row < ch.rows;         // uniform over the wave
-  const int d = a.d, n = a.chi_r;
-  const float2* Wrow = a.W + (size_t)(live ? row : 0) * d * n;
+  const bool live = row < ch.rows;  // uniform over the wave
+  const int n = a.chi_r;
+  const int64_t crow = ch.c0 + row;  // row within the call
+  const float2* Wrow = a.W + (size_t)(live ? row : 0) * ND * n;
   const int r0 = 512 * h + 8 * lane;
   const bool valid = live && r0 < n;
 
-  float2 w[DM][8];
+  float2 w[ND][8];
 #pragma unroll
-  for (int jj = 0; jj < DM; ++jj)
+  for (int jj = 0; jj < ND; ++jj)
 #pragma unroll
     for (int e = 0; e < 8; ++e) w[jj][e] = make_float2(0.f, 0.f);
   if (live) {
     if ((n & 7) == 0) {
       const int rc = min(r0, n - 8);
 #pragma unroll
-      for (int jj = 0; jj < DM; ++jj) {
-        if (jj < d) {
-          const float4* src = reinterpret_cast<const float4*>(Wrow + (size_t)jj * n + rc);
+      for (int jj = 0; jj < ND; ++jj) {
+        const float4* src = reinterpret_cast<const float4*>(Wrow + (size_t)jj * n + rc);
 #pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            const float4 p4 = src[e >> 1];
-            w[jj][e] = make_float2(p4.x, p4.y);
-            w[jj][e + 1] = make_float2(p4.z, p4.w);
-          }
+        for (int e = 0; e < 8; e += 2) {
+          const float4 p4 = src[e >> 1];
+          w[jj][e] = make_float2(p4.x, p4.y);
+          w[jj][e + 1] = make_float2(p4.z, p4.w);
         }
       }
     } else {
 #pragma unroll
-      for (int jj = 0; jj < DM; ++jj)
+      for (int jj = 0; jj < ND; ++jj)
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          if (jj < d && r0 + e < n) w[jj][e] = Wrow[(size_t)jj * n + r0 + e];
+          if (r0 + e < n) w[jj][e] = Wrow[(size_t)jj * n + r0 + e];
     }
   }
-  // D(mu) while the loads are in flight (the sample's first wave)
-  if (live && h == 0) {
-    const float2 mu = a.mu[(size_t)(ch.c0 + row) * a.M + a.site];
-    for (int t = lane; t < d * d; t += 64) Dsh[rl][t] = displacement_entry(mu.x, mu.y, t / d, t % d);
+  // D(mu) and the uniform while the loads are in flight
+  if (live) {
+    if (h == 0) {
+      const float2 mu = a.mu[(size_t)crow * a.M + a.site];
+      displacement4(mu.x, mu.y, ND, lane, pw[rl], Dsh[rl]);
+    } else if (lane == 0) {
+      u_sh[rl] = draw_uniform((uint64_t)(ch.n_offset + crow), a.site, seed, a.mps_id);
+    }
   }
   __syncthreads();
 
   // branch weights of W' (columns past chi_r left out)
   if (live) {
-    const float2* D = Dsh[rl];
-    float qa[DM];
+    float qa[ND];
 #pragma unroll
-    for (int i = 0; i < DM; ++i) qa[i] = 0.f;
+    for (int i = 0; i < ND; ++i) {
+      float2 g[ND];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
+      for (int jj = 0; jj < ND; ++jj) g[jj] = Dsh[rl][i * ND + jj];
+      qa[i] = 0.f;
 #pragma unroll
-      for (int i = 0; i < DM; ++i) {
-        if (i < d) {
-          float xr = 0.f, xi = 0.f;
-#pragma unroll
-          for (int jj = 0; jj < DM; ++jj) {
-            if (jj < d) {
-              const float2 g = D[i * d + jj];
-              xr += g.x * w[jj][e].x - g.y * w[jj][e].y;
-              xi += g.x * w[jj][e].y + g.y * w[jj][e].x;
-            }
-          }
-          qa[i] += valid ? xr * xr + xi * xi : 0.f;
-        }
+      for (int e = 0; e < 8; ++e) {
+        const float2 x = displaced<ND>(g, w, e);
+        qa[i] += valid ? __builtin_fmaf(x.y, x.y, x.x * x.x) : 0.f;
       }
+    }
 #pragma unroll
-    for (int i = 0; i < DM; ++i) {
+    for (int i = 0; i < ND; ++i) {
       double v = (double)qa[i];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+      v = add_xor<32>(v);
+      v = add_xor<16>(v);
+      v = add_xor<8>(v);
+      v = add_xor<4>(v);
+      v = add_xor<2>(v);
+      v = add_xor<1>(v);
       if (lane == 0) qsh[wv][i] = v;
     }
   }
@@ -491,34 +580,29 @@ __global__ __launch_bounds__(256) void measure_disp_pair_kernel(const MeasurePro
 
   // the decision, one lane per sample
   if (live && h == 0 && lane == 0) {
-    const int64_t crow = ch.c0 + row;  // row within the call
     double* const logp = a.logp + (a.logp_in_call ? crow : row);
-    double q[DMAX];
+    double q[ND];
 #pragma unroll
-    for (int i = 0; i < DMAX; ++i) {
-      const int k = i < DM ? i : 0;  // (the index stays in range when unrolled)
-      q[i] = i < DM && i < d ? qsh[2 * rl][k] + qsh[2 * rl + 1][k] : 0.0;
-    }
+    for (int i = 0; i < ND; ++i) q[i] = qsh[2 * rl][i] + qsh[2 * rl + 1][i];
     // S = P_{d-1}, the last of the left-to-right prefix sums P_j = q_0 + .. + q_j
     double S = 0.0;
 #pragma unroll
-    for (int i = 0; i < DMAX; ++i)
-      if (i < d) S += q[i];
+    for (int i = 0; i < ND; ++i) S += q[i];
     const double lp_prev = *logp;
     const bool alive = !(lp_prev == -INFINITY);
     bool ok = alive && isfinite(S) && S > 0.0;
-    const double u = draw_uniform((uint64_t)(ch.n_offset + crow), a.site, seed, a.mps_id);
+    const double u = u_sh[rl];
     int s = 0;
     double Pi = 0.0;
 #pragma unroll
-    for (int i = 0; i < DMAX; ++i) {
-      Pi += q[i];                    // P_i, summed in the same order as S
-      if (i < d && u > Pi / S) ++s;  // C_i = P_i / S;  C_{d-1} == 1
+    for (int i = 0; i < ND; ++i) {
+      Pi += q[i];           // P_i, summed in the same order as S
+      if (u > Pi / S) ++s;  // C_i = P_i / S;  C_{d-1} == 1
     }
-    if (s > d - 1) s = d - 1;
+    if (s > ND - 1) s = ND - 1;
     double qs = 0.0;
 #pragma unroll
-    for (int i = 0; i < DMAX; ++i)
+    for (int i = 0; i < ND; ++i)
       if (i == s) qs = q[i];
     ok = ok && qs > 0.0;
     if (!ok) s = 0;
@@ -530,8 +614,8 @@ __global__ __launch_bounds__(256) void measure_disp_pair_kernel(const MeasurePro
       if (a.emit_probs) {
         double* ep = a.emit_probs + ((size_t)crow * a.M + a.site) * a.emit_dmax;
 #pragma unroll
-        for (int i = 0; i < DMAX; ++i)
-          if (i < d && i < a.emit_dmax) ep[i] = ok ? q[i] / S : NAN;
+        for (int i = 0; i < ND; ++i)
+          if (i < a.emit_dmax) ep[i] = ok ? q[i] / S : NAN;
       }
     }
     s_sh[rl] = ok ? s : -1;
@@ -545,23 +629,16 @@ __global__ __launch_bounds__(256) void measure_disp_pair_kernel(const MeasurePro
   const int s = s_sh[rl];
   const bool ok = s >= 0;
   const float scale = scale_sh[rl];
-  float2 g[DM];
+  float2 g[ND];
 #pragma unroll
-  for (int jj = 0; jj < DM; ++jj) g[jj] = ok && jj < d ? Dsh[rl][s * d + jj] : make_float2(0.f, 0.f);
+  for (int jj = 0; jj < ND; ++jj) g[jj] = ok ? Dsh[rl][s * ND + jj] : make_float2(0.f, 0.f);
   LWriter<OUT> out(a, row);
   if (r0 < n) {
     float2 v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float xr = 0.f, xi = 0.f;
-#pragma unroll
-      for (int jj = 0; jj < DM; ++jj) {
-        if (jj < d) {
-          xr += g[jj].x * w[jj][e].x - g[jj].y * w[jj][e].y;
-          xi += g[jj].x * w[jj][e].y + g[jj].y * w[jj][e].x;
-        }
-      }
-      v[e] = ok && r0 + e < n ? make_float2(__fmul_rn(xr, scale), __fmul_rn(xi, scale)) : make_float2(0.f, 0.f);
+      const float2 x = displaced<ND>(g, w, e);
+      v[e] = ok && r0 + e < n ? make_float2(__fmul_rn(x.x, scale), __fmul_rn(x.y, scale)) : make_float2(0.f, 0.f);
     }
     if constexpr (OUT == kOutF16F6) {
       out.put8(r0, v);
@@ -572,6 +649,20 @@ __global__ __launch_bounds__(256) void measure_disp_pair_kernel(const MeasurePro
     }
   }
   out.pad_from(16 * ((n + 7) >> 3), lane + 64 * h, 128);
+}
+
+template <int OUT>
+__global__ __launch_bounds__(256, 4) void measure_disp_pair_kernel(const MeasureProb* probs, const ChunkArgs* chp,
+                                                                   uint64_t seed, int* nflag) {
+  const ChunkArgs ch = *chp;
+  const MeasureProb a = probs[blockIdx.y];
+  if (blockIdx.x * 2 >= ch.rows) return;  // the whole workgroup
+  switch (a.d) {
+    case 1: return measure_disp_pair<OUT, 1>(a, ch, seed, nflag);
+    case 2: return measure_disp_pair<OUT, 2>(a, ch, seed, nflag);
+    case 3: return measure_disp_pair<OUT, 3>(a, ch, seed, nflag);
+    default: return measure_disp_pair<OUT, 4>(a, ch, seed, nflag);
+  }
 }
 
 // Measurement without displacement, in two phases per workgroup of 64 rows:
