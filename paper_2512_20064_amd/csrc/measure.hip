@@ -894,11 +894,6 @@ __global__ void fill_noise_kernel(void* p, size_t n, int kind, unsigned seed) {
   }
 }
 
-__global__ void zero_int_kernel(int* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 }  // namespace
 
 hipError_t launch_init(int form, const InitProb* probs, int nprob, const ChunkArgs* ch, int grid_rows,
@@ -925,12 +920,6 @@ hipError_t launch_init(int form, const InitProb* probs, int nprob, const ChunkAr
 hipError_t launch_fill_noise(void* p, size_t n, int kind, unsigned seed, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(fill_noise_kernel, dim3(2048), dim3(256), 0, s, p, n, kind, seed);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_int(int* p, int n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_int_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }
 

@@ -567,7 +567,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
   };
   auto scratch_for = [&](int64_t rows, std::vector<ChainBufs>* bufs) -> size_t {
     const int64_t ns = nstate_for(rows);
-    size_t off = align_up(table_for(ns)) + align_up(sizeof(int));
+    size_t off = align_up(table_for(ns)) + align_up(sizeof(int));  // (+ the flag counter, uploaded with the tables)
     for (int b = 0; b < B; ++b) {
       ChainBufs cb;
       off += chain_layout(rows, chains[b].sh, o.precision, ns, off, cb);
@@ -682,7 +682,6 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
 
   char* const base = noalloc ? (char*)fixed : (char*)h->scratch;
   char* const dtab = base;                                  // problem tables
-  int* const nflag = (int*)(base + align_up(table_bytes));  // flagged-sample counter
   auto at = [&](size_t off) -> void* { return base + off; };
 
   // ---- problem tables, one set per left-vector state ----
@@ -799,7 +798,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
   std::vector<mps::ChunkArgs> cargs(nchunks);  // host copies; live until the final synchronisation
   for (int64_t c = 0; c < nchunks; ++c)
     cargs[c] = mps::ChunkArgs{(int)std::min<int64_t>(nc, N - c * nc), 0, c * nc, n_offset};
-  const size_t chunk_off = site_outer ? tab.put(cargs) : tab.put(std::vector<mps::ChunkArgs>(1));
+  const size_t chunk_off = site_outer ? tab.put(cargs) : tab.put(std::vector<mps::ChunkArgs>(1, cargs[0]));
   // small-bond chains: site pointers, bonds and dimensions in the tables, 32
   // samples per workgroup
   size_t small_off = 0, small_start_off = 0;
@@ -896,7 +895,10 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
     mid_blk = tab.put(blks);
     mid_cm = tab.put(cms);
   }
-  if (tab.blob.size() > table_bytes) return fail(MPS_EINVAL, "internal: problem tables exceed their reservation");
+  // flagged-sample counter, zero at the start of every call
+  const size_t nflag_off = tab.put(std::vector<int>(1, 0));
+  int* const nflag = (int*)(dtab + nflag_off);
+  if (tab.blob.size() > align_up(table_bytes) + align_up(sizeof(int))) return fail(MPS_EINVAL, "internal: problem tables exceed their reservation");
   if ((e = hipMemcpyAsync(dtab, tab.blob.data(), tab.blob.size(), hipMemcpyHostToDevice, stream)) != hipSuccess)
     return hip_fail(e, "hipMemcpyAsync (problem tables)");
   const mps::ChunkArgs* const chunk_tab = (const mps::ChunkArgs*)(dtab + chunk_off);
@@ -1101,8 +1103,6 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
 #undef MPS_TRY
 #undef MPS_HIP
 
-  if ((e = mps::launch_zero_int(nflag, 1, stream)) != hipSuccess) return hip_fail(e, "zero kernel");
-
   if (site_outer) {
     // Both slot events start out recorded on the compute stream, so the first
     // two copies wait for nothing but this call's own earlier work.
@@ -1151,7 +1151,9 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
     }
     for (int64_t c = 0; c < nchunks && rc == MPS_OK; ++c) {
       const mps::ChunkArgs& ch = cargs[c];
-      if ((e = hipMemcpyAsync((void*)chunk_tab, &ch, sizeof ch, hipMemcpyHostToDevice, stream)) != hipSuccess) {
+      // (the first chunk's arguments went up with the tables)
+      if (c > 0 &&
+          (e = hipMemcpyAsync((void*)chunk_tab, &ch, sizeof ch, hipMemcpyHostToDevice, stream)) != hipSuccess) {
         rc = hip_fail(e, "hipMemcpyAsync (chunk arguments)");
         break;
       }

@@ -263,7 +263,6 @@ struct DecompressProb {
 size_t stored_bytes(int kind, int chi_l, int d, int chi_r);
 hipError_t launch_decompress(const DecompressProb& p, hipStream_t s);
 
-hipError_t launch_zero_int(int* p, int n, hipStream_t s);
 // n elements of noise of kind 0 (float), 1 (bf16), 2 (fp16), 3 (E4M3 code)
 hipError_t launch_fill_noise(void* p, size_t n, int kind, unsigned seed, hipStream_t s);
 // form: 0 = FP32 path, kBf16x3, kFp16
