@@ -160,7 +160,9 @@ typedef struct {
    * accurate); and, in the split forms, chains whose bonds stay <= 256 and
    * whose sites all have d * ceil(chi_r / 64) <= 16 go through all their
    * sites in one persistent launch with the arithmetic and the bits of the
-   * per-site launches (their sites are packed once per call, up to 1 GiB);
+   * per-site launches (their sites are packed once per call, up to 1 GiB), if
+   * every chain of the call that is left is of this kind; FP32 chains
+   * likewise with d * ceil(chi_r / 64) <= 4 and few samples;
    * 1: every chain takes the per-site launches of the handle's precision
    * form.                                                                   */
   int32_t fused_small;

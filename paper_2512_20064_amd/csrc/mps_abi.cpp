@@ -242,11 +242,17 @@ struct Tables {
 
 // Medium-bond chains (sweep_mid.hip): largest packed size of a call's chains.
 constexpr size_t kMidPackedBytes = size_t(1) << 30;
+// FP32: most samples, over all chains, that take it.  Against the
+// per-site launches (chi 48 .. 128, up to 8 units, 14 sites): 1.8 to 2.8 times
+// as fast at 512 and 4096 samples, 1.4 to 1.9 at 16384, 0.95 to 1.05 at 65536,
+// where the per-site tiles fill the chip.
+constexpr int64_t kMidRowsF32 = 49152;
 
 // Whether every site of a chain fits the persistent medium-bond kernel.
-bool mid_eligible(const Chain& c) {
+bool mid_eligible(const Chain& c, int precision) {
+  const int most = precision == MPS_FP32 ? mps::kMidUnits / 2 : mps::kMidGroups;
   for (int k = 0; k < c.M; ++k)
-    if (mps::mid_groups(c.d[k], c.chi[k + 1]) > mps::kMidGroups) return false;
+    if (mps::mid_groups(c.d[k], c.chi[k + 1]) > most) return false;
   return c.sh.chimax <= mps::kMidChi;
 }
 // Kernel variant of an eligible chain: 0 (up to 4 groups: 4 waves of one group
@@ -273,6 +279,7 @@ MidPack mid_pack(int K, int d, int chi_r, int precision) {
   return m;
 }
 size_t mid_bytes(const Chain& c, int precision) {
+  if (precision == MPS_FP32) return 0;  // the site tensors are read as they are
   size_t b = 0;
   for (int k = 0; k < c.M; ++k) b += mid_pack(c.chi[k], c.d[k], c.chi[k + 1], precision).bytes;
   return b;
@@ -584,34 +591,35 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       return fail(MPS_ENOMEM, "scratch for %lld-sample chunks (%zu B) plus site staging (%zu B) exceeds "
                   "%s (%lld B)", (long long)nc, scratch_for(nc, nullptr), stage_need, cap_name, (long long)cap);
   }
-  // ---- chains for the persistent medium-bond kernel ----
-  // Split forms, device-resident complex64 sites, no displacement,
-  // every site within the kernel's registers and LDS (mid_eligible): the site
-  // tensors are packed once for the call and the whole chain goes through all
-  // its sites in one launch per chunk (sweep_mid.hip), with the bits of the
-  // per-site launches.  The chunk is planned as for the per-site launches; a
-  // capped call takes this path only if every chain can and the packed sites
-  // fit, so that what fits under a cap does not change.
-  std::vector<Chain> mids, big_chains;
-  if (split && o.fused_small == 0 && !any_staged && !(single && o.displace)) {
+  // ---- the persistent medium-bond kernel ----
+  // Split forms, and FP32 with few samples; device-resident complex64 sites,
+  // no displacement, every site of every chain within the kernel's registers
+  // and LDS (mid_eligible): the site tensors are packed once for the call
+  // (FP32 reads them as they are) and each chain goes through all its sites in
+  // one launch per chunk (sweep_mid.hip), with the bits of the per-site
+  // launches.  A batch where some chains don't fit keeps the per-site launches
+  // for all: those of the chains that don't fit run anyway, mostly waiting,
+  // and carry the others along (6 and 24 chains, 20 to 40 sites, chi <= 400,
+  // fp16f6, the chains that fit taken out of the launches: 3470 us against
+  // 2630 and 5300 against 5250 at 1500 samples, 4770 against 4450 and 10770
+  // against 11290 at 5000; 24 chains, 64 samples: 4490 against 2880).  The
+  // chunk is planned as for the per-site launches, and a capped call takes
+  // this path only if the packed sites fit, so that what fits under a cap does
+  // not change.
+  std::vector<Chain> mids;
+  if ((split || !lowp) && o.fused_small == 0 && !any_staged && !(single && o.displace) && !chains.empty()) {
     size_t packed = 0;
+    bool fits = lowp || (int64_t)chains.size() * nc <= kMidRowsF32;
     for (const Chain& c : chains) {
-      const size_t bytes = mid_eligible(c) ? mid_bytes(c, o.precision) : 0;
-      if (bytes && packed + bytes <= kMidPackedBytes) {
-        packed += bytes;
-        mids.push_back(c);
-      } else {
-        big_chains.push_back(c);
-      }
+      fits = fits && mid_eligible(c, o.precision);
+      if (fits) packed += mid_bytes(c, o.precision);
     }
-    if (!mids.empty() && cap > 0 &&
-        (!big_chains.empty() || (int64_t)(packed + align_up(table_for(1)) + 1024) > cap)) {
-      mids.clear();
-    } else if (!mids.empty()) {
-      chains.swap(big_chains);
-      B = (int)chains.size();
+    fits = fits && packed <= kMidPackedBytes &&
+           (cap == 0 || (int64_t)(packed + align_up(table_for(1)) + 1024) <= cap);
+    if (fits) {
+      mids.swap(chains);
+      B = 0;
       Mmax = 0;
-      for (const Chain& c : chains) Mmax = std::max(Mmax, c.M);
     }
   }
   const int nmid = (int)mids.size();
@@ -852,11 +860,15 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       std::vector<mps::MidChain> mc;
       std::vector<int> starts(1, 0);
       for (const Chain& c : mids) {
-        if (mid_variant(c) != w) continue;
+        if ((lowp ? mid_variant(c) : 0) != w) continue;
         std::vector<mps::MidSite> ms(c.M);
         for (int k = 0; k < c.M; ++k) {
           const int K = c.chi[k], dk = c.d[k], chr = c.chi[k + 1];
           const int CP = mps::lp_pad_cols(chr, mps::kTileNarrow), Kp = mps::lp_pad_k(K);
+          if (!lowp) {
+            ms[k] = mps::MidSite{c.tensors[k], nullptr, nullptr, K, Kp, dk, chr, CP, 0};
+            continue;
+          }
           const MidPack m = mid_pack(K, dk, chr, o.precision);
           char* const q = base + off;
           float* const cs = m.cs ? (float*)(q + 2 * m.plane) : nullptr;
@@ -1042,7 +1054,12 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
   };
   auto run_mid = [&](const mps::ChunkArgs* ch) -> int {
     MPS_TRY(mark_fused(1, 0));
-    for (int w = 2; w >= 0; --w)
+    if (!lowp)
+      MPS_HIP(mps::launch_sweep_mid_f32((const mps::MidChain*)tp(mid_launch[0].chains),
+                                        (const int*)tp(mid_launch[0].starts), mid_launch[0].n, mid_launch[0].items,
+                                        mid_launch[0].chimax, ch, seed, nflag, stream),
+              "medium-bond sweep launch");
+    for (int w = 2; w >= 0 && lowp; --w)
       MPS_HIP(mps::launch_sweep_mid(form, 4 << w, (const mps::MidChain*)tp(mid_launch[w].chains),
                                     (const int*)tp(mid_launch[w].starts), mid_launch[w].n, mid_launch[w].items,
                                     mid_launch[w].chimax, ch, seed, nflag, stream),
@@ -1128,8 +1145,10 @@ int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offse
       }
     }
   } else {
-    if (nmid && (rc = run_mid_pack())) return rc;
-    st.pack_launches += nmid ? 1 : 0;
+    if (nmid && lowp) {
+      if ((rc = run_mid_pack())) return rc;
+      st.pack_launches++;
+    }
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     if (use_graph) {

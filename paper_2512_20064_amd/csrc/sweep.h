@@ -213,12 +213,13 @@ struct SmallChain {
 hipError_t launch_sweep_small(const SmallChain* chains, const int* item_start, int nchain, int items,
                               const ChunkArgs* ch, uint64_t seed, int* nflag, hipStream_t s);
 
-// Persistent medium-bond sweep (the split forms): chains whose sites all
+// Persistent medium-bond sweep (the split forms and FP32): chains whose sites all
 // have at most kMidGroups groups of 64 complex columns (d * ceil(chi_r / 64))
 // and bonds <= kMidChi, 32 samples per workgroup.
 constexpr int kMidRows = 32;
 constexpr int kMidGroups = 16;
 constexpr int kMidChi = 256;
+constexpr int kMidUnits = 8;  // FP32: units of 32 complex columns of a site (two per group)
 __host__ __device__ inline int mid_groups(int d, int chi_r) { return d * (lp_pad_cols(chi_r, kTileNarrow) / 64); }
 // LDS of a workgroup: the operand planes of 32 left vectors, 32 rows of a
 // branch, 2 complex apart so that 16-byte accesses down the rows spread over
@@ -251,6 +252,9 @@ struct MidChain {
 // launch_sweep_small.
 hipError_t launch_sweep_mid(int form, int groups, const MidChain* chains, const int* item_start, int nchain, int items,
                             int chimax, const ChunkArgs* ch, uint64_t seed, int* nflag, hipStream_t s);
+// FP32: MidSite::Bh is the complex64 site tensor itself.
+hipError_t launch_sweep_mid_f32(const MidChain* chains, const int* item_start, int nchain, int items, int chimax,
+                                const ChunkArgs* ch, uint64_t seed, int* nflag, hipStream_t s);
 
 // Stored site tensor (device memory) -> complex64 site tensor.
 struct DecompressProb {

@@ -85,13 +85,15 @@ def test_medium_bond_kernel_edges(form, case):
     b.close()
 
 
-def test_medium_bond_kernel_batch_and_chunks():
+@pytest.mark.parametrize("extra", [[], [([2] * 14, 300)]])
+def test_medium_bond_kernel_batch_and_chunks(extra):
     """Chains of every kernel variant in one batched call with a ragged last
-    chunk, against one call per chain on the per-site launches."""
+    chunk, without and with a chain that does not fit the kernel (all per-site
+    then), against one call per chain on the per-site launches."""
     from paper_2512_20064_amd import mps
     from tests.parity_util import upload
     print("[gpu-case] medium-bond batch", flush=True)
-    specs = [([4] * 5, 16), ([4] * 9, 64), ([3] * 11, 100), ([4] * 8, 200), ([2] * 14, 300)]
+    specs = [([4] * 5, 16), ([4] * 9, 64), ([3] * 11, 100), ([4] * 8, 200)] + extra
     chains = [upload(synth.to_c64(synth.random_mps(90 + i, d, synth.ramp_bonds(d, c)))) for i, (d, c) in
               enumerate(specs)]
     s = mps.Sampler(0, precision="fp16f6", n_chunk=100)
@@ -137,3 +139,35 @@ def test_fp32_direct_tile_edges(d, chi, N):
     for r in (shifted, narrow):
         assert torch.equal(r["outcomes"], wide["outcomes"]) and torch.equal(r["logp"], wide["logp"])
     s.close()
+
+
+@pytest.mark.parametrize("d,chi,N,first", [
+    ([4] * 9, [1, 4, 16, 64, 64, 61, 64, 16, 4, 1], 33, 0),        # 8 units, an odd bond
+    ([2] * 18, [1, 2, 4, 8, 16, 32, 64, 65, 97, 128, 127, 90, 64, 32, 16, 8, 4, 2, 1], 31, 7),  # over a block of 16 sites
+    ([3, 13, 2], [1, 3, 4, 2], 20, 0),                               # 26 units of small bonds: per site
+    ([4, 4, 1, 1, 1, 1], [1, 4, 16, 16, 16, 16, 16], 1, 1 << 33),
+    ([2, 2, 2, 2, 2, 2, 1], [1, 2, 4, 8, 16, 32, 50, 200], 70, 0),  # an open right end wider than the plateau
+    ([8, 5, 1], [1, 8, 40, 41], 40, 0),                              # 16 and 10 units: per site
+])
+def test_fp32_medium_bond_kernel_edges(d, chi, N, first):
+    """FP32: the persistent medium-bond kernel (where the chain's sites fit it)
+    gives the bits of the per-site launches, and agrees with the oracle."""
+    from paper_2512_20064_amd import mps
+    from tests.parity_util import EPS_FP32, upload
+    print(f"[gpu-case] fp32 medium-bond edges chi={chi} N={N}", flush=True)
+    t = synth.to_c64(synth.random_mps(71, d, chi))
+    small = max(chi) <= 32 and max(d) <= 4  # those take the small-bond kernel: other sums
+    a, b = mps.Sampler(0), mps.Sampler(0, fused_small=False)
+    dev = upload(t)
+    ra = a.sample(dev, N, 77, n_offset=first, emit_n=N)
+    rb = b.sample(dev, N, 77, n_offset=first, emit_n=N)
+    torch.cuda.synchronize()
+    if not small:
+        if all(x * -(-c // 64) <= 4 for x, c in zip(d, chi[1:])):
+            assert a.stats.scratch_bytes < b.stats.scratch_bytes  # no W in memory
+        assert a.stats.contract_launches == b.stats.contract_launches == len(d)
+        for key in ("outcomes", "logp", "probs", "u"):
+            assert torch.equal(torch.nan_to_num(ra[key]), torch.nan_to_num(rb[key])), key
+    _check(t, a, N, first, EPS_FP32)
+    a.close()
+    b.close()
