@@ -244,9 +244,10 @@ struct Tables {
 constexpr size_t kMidPackedBytes = size_t(1) << 30;
 // FP32: most samples, over all chains, that take it.  Against the
 // per-site launches (chi 48 .. 128, up to 8 units, 14 sites): 1.8 to 2.8 times
-// as fast at 512 and 4096 samples, 1.4 to 1.9 at 16384, 0.95 to 1.05 at 65536,
-// where the per-site tiles fill the chip.
-constexpr int64_t kMidRowsF32 = 49152;
+// as fast at 512 and 4096 samples, 1.4 to 1.9 at 16384, 1.08 to 1.29 at 32768,
+// 0.97 to 1.09 at 48000 and 0.95 to 1.05 at 65536, where the per-site tiles
+// fill the chip.
+constexpr int64_t kMidRowsF32 = 40960;
 
 // Whether every site of a chain fits the persistent medium-bond kernel.
 bool mid_eligible(const Chain& c, int precision) {

@@ -15,11 +15,12 @@
 // d = 4: 16000 cycles a site) and decision follow each other; with enough
 // samples for the per-site tiles to fill the chip those are as fast
 // (kMidRowsF32).  14 sites, 4096 samples, whole calls against per-site
-// launches: chi = 64, d = 2 158 us against 418, d = 4 226 against 452;
-// chi = 128, d = 2 272 against 510.  With up to four units per wave one after
-// the other (W of chi = 256, d = 4 in registers) it lost from 12 units on
-// (chi = 128, d = 4: 690 us against 547); held to 128 registers for two
-// workgroups per CU it spills (d = 4, chi = 64: 500 us).
+// launches: chi = 64, d = 2 157 us against 422, d = 4 226 against 451;
+// chi = 128, d = 2 271 against 504.  With up to four units per wave one after
+// the other (W of chi = 256, d = 4 in registers) it lost from 16 units on
+// (512 samples, chi = 100 and 128, d = 4: 546 us against 521, 692 against
+// 547) and took 212 us where this takes 158 (chi = 64, d = 2); held to 128
+// registers for two workgroups per CU it spills 692 bytes per lane (294 us).
 
 #include "lp_ops.h"
 #include "philox.h"
