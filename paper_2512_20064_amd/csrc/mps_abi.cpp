@@ -42,6 +42,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -433,7 +434,8 @@ class PtrClassifier {
 // noalloc: run in the fixed device array `scratch` (mps_sample_noalloc)
 // instead of the handle's allocations; no HIP allocation of any kind is made
 // (no profiling events, no graph, no staging).
-int run_sweep(mps_ctx* h, std::vector<Chain>& chains, int64_t N, int64_t n_offset, uint64_t seed, bool single,
+// chains: a copy, which the routes below take chains out of.
+int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset, uint64_t seed, bool single,
               int kind, bool noalloc = false) {
   const mps_options& o = h->opt;
   // Cap on the scratch: the caller's max_device_bytes, and for noalloc the
@@ -1310,7 +1312,7 @@ int mps_sample(mps_handle h, const void* const* tensors, int32_t dtype, const in
     return MPS_OK;
   }
   if (!outcomes) return fail(MPS_EINVAL, "outcomes is NULL");
-  return run_sweep(h, chains, N, n_offset, seed, true, dtype);
+  return run_sweep(h, std::move(chains), N, n_offset, seed, true, dtype);
 }
 
 int mps_sample_noalloc(mps_handle h, const void* const* tensors, int32_t dtype, const int32_t* chi, const int32_t* d,
@@ -1326,7 +1328,7 @@ int mps_sample_noalloc(mps_handle h, const void* const* tensors, int32_t dtype, 
     return MPS_OK;
   }
   if (!outcomes) return fail(MPS_EINVAL, "outcomes is NULL");
-  return run_sweep(h, chains, N, n_offset, seed, true, dtype, true);
+  return run_sweep(h, std::move(chains), N, n_offset, seed, true, dtype, true);
 }
 
 int mps_sample_batch(mps_handle h, int32_t B, const mps_chain* chains_in, int32_t dtype, int64_t N,
@@ -1348,7 +1350,7 @@ int mps_sample_batch(mps_handle h, int32_t B, const mps_chain* chains_in, int32_
     h->st.scratch_bytes = (int64_t)h->scratch_bytes;
     return MPS_OK;
   }
-  return run_sweep(h, chains, N, n_offset, seed, false, dtype);
+  return run_sweep(h, std::move(chains), N, n_offset, seed, false, dtype);
 }
 
 int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const int32_t* chi, const int32_t* d,

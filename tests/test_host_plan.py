@@ -1,0 +1,103 @@
+"""Planning in the C ABI's host code (routes, scratch, launches, messages), run
+on the CPU: mps_abi.cpp linked with a stand-in for the HIP runtime and the
+kernel launches (host_hip.cpp), which logs every launch."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2512_20064_amd import build, mps, synth
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host_lib(tmp_path_factory):
+    cc = build.hipcc()
+    if shutil.which(cc) is None and not os.path.exists(cc):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("host")
+    objs = []
+    for src in (os.path.join(build.CSRC, "mps_abi.cpp"), os.path.join(HERE, "host_hip.cpp")):
+        objs.append(str(d / (os.path.basename(src) + ".o")))
+        subprocess.run([cc, "-O1", "-std=c++17", f"--offload-arch={build.ARCH}", "-fPIC",
+                        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                        "-x", "hip", "-c", src, "-o", objs[-1]], check=True, capture_output=True)
+    lib = str(d / "libmps_host.so")
+    # (-Bsymbolic: a HIP runtime that torch has loaded does not come first)
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", *objs, "-lpthread", "-o", lib], check=True,
+                   capture_output=True)
+    return lib
+
+
+@pytest.fixture
+def host(host_lib, monkeypatch):
+    monkeypatch.setattr(mps, "_lib", None)
+    lib = mps.load(host_lib)
+    lib.host_log.restype = ctypes.c_char_p
+    lib.host_peak.restype = ctypes.c_size_t
+    lib.host_reset.argtypes = [ctypes.c_size_t]
+    lib.host_set_pinned.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    lib.host_reset(1 << 40)
+    return lib
+
+
+def _log(lib):
+    """The launches since the last call, [(kind, {field: value})]."""
+    out = [(ln.split()[0], {k: int(v) for k, v in re.findall(r"(\w+)=(\d+)", ln)})
+           for ln in lib.host_log().decode().splitlines()]
+    lib.host_clear_log()
+    return out
+
+
+def _handle(precision, **kw):
+    o = mps.mps_options_init()
+    o.precision = mps.PRECISIONS[precision]
+    for k, v in kw.items():
+        setattr(o, k, v)
+    return mps.mps_create(0, o), o
+
+
+def _sites(M):
+    """Site pointers that are never read (device memory, extent unknown)."""
+    return [0x10000000 + 0x1000 * k for k in range(M)]
+
+
+def _sample(h, chi, d, N):
+    M = len(d)
+    return mps.mps_sample(h, _sites(M), mps.MPS_C64, chi, d, M, N, 0, 1, 0x1000, 0)
+
+
+def _autotune(h, chi, d, N, tensors=None):
+    M = len(d)
+    return mps.mps_autotune(h, tensors or _sites(M), mps.MPS_C64, chi, d, M, N, 1)
+
+
+# one warm-up and three timed sweeps of a candidate
+SWEEPS = 4
+
+
+@pytest.mark.parametrize("form,d,cap,kind", [
+    ("bf16x3", [4] * 16, 128, "mid"),
+    ("fp16f6", [4] * 16, 256, "mid"),
+    ("fp32", [2] * 16, 100, "mid"),
+    ("fp32", [4] * 12, 32, "small"),
+    ("fp16f8", [4] * 12, 32, "small"),
+    ("fp32", [4] * 16, 256, "contract"),
+])
+def test_autotune_times_the_chain_in_every_candidate(host, form, d, cap, kind):
+    """Every timed sweep of every candidate launches the probe's sites."""
+    chi = synth.ramp_bonds(d, cap)
+    h, _ = _handle(form)
+    rc, rep = _autotune(h, chi, d, 40000)
+    assert rc == 0, mps.mps_last_error()
+    log = [x for x in _log(host) if x[0] == kind]
+    sites = rep.probe_sites if kind == "contract" else 1
+    for rows in (8192, 16384, 32768, 40000):
+        n = sum(f["rows"] == rows for _, f in log)
+        assert n >= SWEEPS * sites and n % (SWEEPS * sites) == 0, (rows, n)
+    assert rep.candidates == 16 and rep.skipped == 0
+    mps.mps_destroy(h)
