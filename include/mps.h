@@ -312,7 +312,8 @@ typedef struct {
   int64_t n_chunk;        /* chosen samples per chunk                               */
   int32_t tile_group;     /* chosen contraction tile order (see mps_options)        */
   int32_t probe_sites;    /* sites 0 .. probe_sites-1 formed the probe              */
-  int32_t candidates;     /* (n_chunk, tile_group) pairs timed                      */
+  int32_t candidates;     /* (n_chunk, tile_group) pairs timed (a chunk on a        */
+                          /* persistent kernel: once for all its tile orders)       */
   int32_t skipped;        /* pairs skipped for lack of device memory                */
   double rate;            /* probe site-samples/s of the chosen pair                */
   double default_rate;    /* probe site-samples/s of the library defaults (0: not timed) */
@@ -324,7 +325,8 @@ typedef struct {
  *
  * The probe is the chain's prefix up to and including the first site of
  * largest per-sample work chi[k]*d[k]*chi[k+1] (the plateau shape, which
- * dominates the sweep, together with the ramp that leads to it).  Every pair
+ * dominates the sweep, together with the ramp that leads to it), on the
+ * kernels that the whole chain takes with the handle's options.  Every pair
  * of n_chunk in {8192, 16384, 32768, 65536, 131072, 262144} (capped at N)
  * and tile_group in {1, 2, 4, 8} is timed as one warm-up and three timed
  * single-chunk sweeps over the probe (wall clock around the synchronous

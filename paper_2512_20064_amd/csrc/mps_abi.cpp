@@ -322,6 +322,7 @@ struct mps_ctx {
   hipEvent_t ev_expand[2] = {nullptr, nullptr};
   std::vector<hipEvent_t> events;
   mps_stats st{};
+  bool per_site = false;  // the last sweep had chains on the per-site launches
   // contraction tile per site shape (chi_l, d, chi_r, rows per launch), set by
   // mps_autotune_tiles or mps_set_tiles; shapes not listed take the wide tile
   std::map<std::array<int64_t, 4>, int> tiles;
@@ -434,9 +435,11 @@ class PtrClassifier {
 // noalloc: run in the fixed device array `scratch` (mps_sample_noalloc)
 // instead of the handle's allocations; no HIP allocation of any kind is made
 // (no profiling events, no graph, no staging).
-// chains: a copy, which the routes below take chains out of.
+// chains: a copy, which the routes below take chains out of.  job: the chain
+// that decides on the route (a single chain's probe is a prefix of it), NULL
+// for each chain itself.
 int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset, uint64_t seed, bool single,
-              int kind, bool noalloc = false) {
+              int kind, bool noalloc = false, const Chain* job = nullptr) {
   const mps_options& o = h->opt;
   // Cap on the scratch: the caller's max_device_bytes, and for noalloc the
   // size of the fixed array.
@@ -543,9 +546,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   if (o.fused_small == 0 && !any_staged && !(single && o.displace)) {
     std::vector<Chain> bigs;
     for (const Chain& c : chains) {
-      int dmax = 0;
-      for (int k = 0; k < c.M; ++k) dmax = std::max(dmax, (int)c.d[k]);
-      (c.sh.chimax <= mps::kSmallChi && dmax <= mps::kSmallD ? smalls : bigs).push_back(c);
+      const Chain& r = job ? *job : c;
+      (small_chain(o, r.chi, r.d, r.M) ? smalls : bigs).push_back(c);
     }
     chains.swap(bigs);
     B = (int)chains.size();
@@ -614,8 +616,9 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
     size_t packed = 0;
     bool fits = lowp || (int64_t)chains.size() * nc <= kMidRowsF32;
     for (const Chain& c : chains) {
-      fits = fits && mid_eligible(c, o.precision);
-      if (fits) packed += mid_bytes(c, o.precision);
+      const Chain& r = job ? *job : c;
+      fits = fits && mid_eligible(r, o.precision);
+      if (fits) packed += mid_bytes(r, o.precision);
     }
     fits = fits && packed <= kMidPackedBytes &&
            (cap == 0 || (int64_t)(packed + align_up(table_for(1)) + 1024) <= cap);
@@ -626,6 +629,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
     }
   }
   const int nmid = (int)mids.size();
+  h->per_site = B > 0;
   double mid_flops_per_row = 0.0, mid_meas_bytes_per_row = 0.0;
   int Mmid = 0;
   size_t mid_data = 0, mid_tables = 0;
@@ -1373,11 +1377,12 @@ int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const 
     }
   }
   const int Mp = kp + 1;
+  const Chain job = chains[0];
   chains[0].M = Mp;
   if ((rc = validate_chain(chains[0], h->opt.precision, chains[0].sh, 0))) return rc;
 
   const int64_t chunk_set[] = {8192, 16384, 32768, 65536, 131072, 262144};
-  const int group_set[] = {1, 2, 4, 8};
+  const int group_set[] = {kDefaultGroup, 1, 2, 8};
   std::vector<int64_t> ncs;
   for (int64_t c : chunk_set)
     if (c <= N) ncs.push_back(c);
@@ -1400,7 +1405,12 @@ int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const 
   chains[0].outcomes = outc;
   chains[0].logp = lp;
 
+  // What takes the whole job to the per-site launches takes the probe there:
+  // a displacement (off during the probe), a staged site past the prefix.
   const mps_options saved = h->opt;
+  bool per_site = saved.fused_small != 0 || saved.displace != nullptr || dtype != MPS_C64;
+  PtrClassifier where;
+  for (int k = Mp; k < M && !per_site; ++k) per_site = where.classify(tensors[k]).type == hipMemoryTypeHost;
   mps_tune_report r{};
   r.probe_sites = Mp;
   int64_t best_nc = 0;
@@ -1419,7 +1429,8 @@ int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const 
       h->opt.emit_probs = nullptr;
       h->opt.emit_u = nullptr;
       h->opt.displace = nullptr;
-      int rr = run_sweep(h, chains, nc, 0, seed, true, dtype);
+      h->opt.fused_small = per_site ? 1 : 0;
+      int rr = run_sweep(h, chains, nc, 0, seed, true, dtype, false, &job);
       if (rr == MPS_ENOMEM) {
         r.skipped++;
         continue;
@@ -1430,7 +1441,7 @@ int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const 
       }
       const auto t0 = std::chrono::steady_clock::now();
       for (int rep_i = 0; rep_i < kTuneReps && (rr == MPS_OK || rr == MPS_ENUMERIC); ++rep_i)
-        rr = run_sweep(h, chains, nc, 0, seed, true, dtype);
+        rr = run_sweep(h, chains, nc, 0, seed, true, dtype, false, &job);
       const double dt = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
       if (rr != MPS_OK && rr != MPS_ENUMERIC) {
         err = rr;
@@ -1443,6 +1454,10 @@ int mps_autotune(mps_handle h, const void* const* tensors, int32_t dtype, const 
         best = rate;
         best_nc = nc;
         best_g = g;
+      }
+      if (!h->per_site) {  // the persistent kernels have no tile order
+        r.candidates += (int32_t)(sizeof group_set / sizeof *group_set) - 1;
+        break;
       }
     }
     if (err) break;

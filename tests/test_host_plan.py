@@ -101,3 +101,43 @@ def test_autotune_times_the_chain_in_every_candidate(host, form, d, cap, kind):
         assert n >= SWEEPS * sites and n % (SWEEPS * sites) == 0, (rows, n)
     assert rep.candidates == 16 and rep.skipped == 0
     mps.mps_destroy(h)
+
+
+def _plateau(M, d, chi):
+    return synth.ramp_bonds([d] * M, chi)
+
+
+@pytest.mark.parametrize("name,form,chi,d,want", [
+    # packed sites of the whole chain above the limit of the persistent kernel
+    ("packed", "bf16x3", _plateau(600, 4, 256), [4] * 600, "contract"),
+    ("fits", "bf16x3", _plateau(60, 4, 256), [4] * 60, "mid"),
+    # the largest site lies in a small-bond prefix, a bond of 33 follows
+    ("wider later", "bf16x3", [1, 4, 16, 32, 32, 16, 33, 33, 33], [4, 4, 4, 4, 2, 4, 2, 1], "mid"),
+    ("wider later", "fp16", [1, 4, 16, 32, 32, 16, 33, 33, 33], [4, 4, 4, 4, 2, 4, 2, 1], "contract"),
+    # displaced, or some later site in host memory: per site
+    ("displaced", "fp16f6", _plateau(16, 4, 64), [4] * 16, "contract"),
+    ("displaced", "fp32", _plateau(12, 4, 16), [4] * 12, "contract"),
+    ("pinned tail", "fp16f6", _plateau(16, 4, 64), [4] * 16, "contract"),
+])
+def test_autotune_probe_takes_the_kernels_of_the_job(host, name, form, chi, d, want):
+    M, N = len(d), 20000
+    h, o = _handle(form, displace=0x1000 if name == "displaced" else None)
+    sites = _sites(M)
+    if name == "pinned tail":
+        host.host_set_pinned(sites[-1], sites[-1] + 1)
+    rc, rep = _autotune(h, chi, d, N, sites)
+    assert rc == 0, mps.mps_last_error()
+    log = _log(host)
+    kinds = {k for k, _ in log} & {"small", "mid", "contract"}
+    assert kinds == {want} and rep.candidates == 12 and rep.probe_sites < M
+    if want != "contract":  # no tile order to time: once per chunk, the default kept
+        for rows in (8192, 16384, 20000):
+            assert sum(k == want and f["rows"] == rows for k, f in log) == SWEEPS
+        assert rep.tile_group == 4
+    if name in ("packed", "fits", "displaced"):  # and it is the job's own route
+        if name == "displaced":
+            o.displace = 0x1000
+            mps.mps_set_options(h, o)
+        assert _sample(h, chi, d, 100) == 0, mps.mps_last_error()
+        assert {k for k, _ in _log(host)} & {"small", "mid", "contract"} == {want}
+    mps.mps_destroy(h)
