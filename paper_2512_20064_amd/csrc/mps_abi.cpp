@@ -609,40 +609,46 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   // 2630 and 5300 against 5250 at 1500 samples, 4770 against 4450 and 10770
   // against 11290 at 5000; 24 chains, 64 samples: 4490 against 2880).  The
   // chunk is planned as for the per-site launches, and a capped call takes
-  // this path only if the packed sites fit, so that what fits under a cap does
-  // not change.
+  // this path only if its tables and packed sites fit, so that what fits under
+  // a cap does not change.
   std::vector<Chain> mids;
+  size_t mid_data = 0;  // packed sites
   if ((split || !lowp) && o.fused_small == 0 && !any_staged && !(single && o.displace) && !chains.empty()) {
-    size_t packed = 0;
+    size_t packed = 0, tables = 0;
     bool fits = lowp || (int64_t)chains.size() * nc <= kMidRowsF32;
     for (const Chain& c : chains) {
       const Chain& r = job ? *job : c;
       fits = fits && mid_eligible(r, o.precision);
       if (fits) packed += mid_bytes(r, o.precision);
+      mid_data += mid_bytes(c, o.precision);
+      tables += mid_table_bytes(c);
     }
-    fits = fits && packed <= kMidPackedBytes &&
-           (cap == 0 || (int64_t)(packed + align_up(table_for(1)) + 1024) <= cap);
-    if (fits) {
+    fits = fits && packed <= kMidPackedBytes;
+    // the plan with the chains on this path, given up if it is over the cap
+    const int B0 = B, M0 = Mmax;
+    mids.swap(chains);
+    B = 0;
+    Mmax = 0;
+    small_bytes += tables;
+    if (!fits || (cap > 0 && (int64_t)(scratch_for(nc, nullptr) + packed) > cap)) {
       mids.swap(chains);
-      B = 0;
-      Mmax = 0;
+      B = B0;
+      Mmax = M0;
+      small_bytes -= tables;
+      mid_data = 0;
     }
   }
   const int nmid = (int)mids.size();
   h->per_site = B > 0;
   double mid_flops_per_row = 0.0, mid_meas_bytes_per_row = 0.0;
   int Mmid = 0;
-  size_t mid_data = 0, mid_tables = 0;
   for (const Chain& c : mids) {
-    mid_data += mid_bytes(c, o.precision);
-    mid_tables += mid_table_bytes(c);
     Mmid = std::max(Mmid, c.M);
     for (int k = 0; k < c.M; ++k) {
       mid_flops_per_row += 8.0 * c.chi[k] * c.d[k] * c.chi[k + 1];
       mid_meas_bytes_per_row += mps::mid_groups(c.d[k], c.chi[k + 1]) * 4.0 + 2.0 * c.chi[k + 1] * 8 + 4 + 16;
     }
   }
-  small_bytes += mid_tables;
   std::vector<ChainBufs> bufs(B);
   const size_t mid_at = scratch_for(nc, &bufs);
   const size_t total = mid_at + mid_data;

@@ -141,3 +141,37 @@ def test_autotune_probe_takes_the_kernels_of_the_job(host, name, form, chi, d, w
         assert _sample(h, chi, d, 100) == 0, mps.mps_last_error()
         assert {k for k, _ in _log(host)} & {"small", "mid", "contract"} == {want}
     mps.mps_destroy(h)
+
+
+def _batch(h, shapes, N):
+    """mps_sample_batch over chains of (chi, d); pointers are never read."""
+    descs, keep = [], []
+    for b, (chi, d) in enumerate(shapes):
+        c, k = mps.make_chain(_sites(len(d)), chi, d, b, 0x1000, None)
+        descs.append(c)
+        keep.append(k)
+    return mps.mps_sample_batch(h, descs, mps.MPS_C64, N, 0, 1)
+
+
+@pytest.mark.parametrize("form", ["fp32", "bf16x3", "fp16f6"])
+@pytest.mark.parametrize("B,M,N", [(100, 8, 64), (300, 4, 10), (1, 4, 1), (3, 30, 500)])
+def test_scratch_stays_under_the_cap(host, form, B, M, N):
+    """Whatever route a call takes, the memory it allocates stays within
+    max_device_bytes, and the caps and chunks that are accepted are those of
+    the per-site launches."""
+    d = [4] * M
+    chi = [1, 4, 16, 40] + [40] * (M - 3)
+    routes = set()
+    for i in range(70):
+        cap = int(20000 * 1.2 ** i)
+        got = []
+        for fused in (0, 1):
+            host.host_reset(1 << 40)
+            h, _ = _handle(form, max_device_bytes=cap, fused_small=fused)
+            rc = _batch(h, [(chi, d)] * B, N)
+            got.append((rc, mps.mps_get_stats(h).n_chunk))
+            assert host.host_peak() <= cap, (cap, host.host_peak())
+            routes |= {k for k, _ in _log(host)}
+            mps.mps_destroy(h)
+        assert got[0] == got[1], (cap, got)
+    assert {"mid", "contract"} <= routes
