@@ -450,7 +450,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   const bool lowp = o.precision != MPS_FP32;
   const bool split = is_split(o.precision);
   const int form = lowp ? lp_form(o.precision) : 0;
-  int B = (int)chains.size();
+  const int64_t nchain = (int64_t)chains.size();
+  int B = (int)nchain;  // chains on the per-site launches
   int Mmax = 0;
   for (const Chain& c : chains) Mmax = std::max(Mmax, c.M);
 
@@ -1227,7 +1228,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   h->st = st;
   if (flagged > 0)
     return fail(MPS_ENUMERIC, "%d of %lld samples met S <= 0 or a non-finite S (outcome -1, logp -inf)", flagged,
-                (long long)N * B);
+                (long long)(N * nchain));
   g_err.clear();
   return MPS_OK;
 }

@@ -175,3 +175,20 @@ def test_scratch_stays_under_the_cap(host, form, B, M, N):
             mps.mps_destroy(h)
         assert got[0] == got[1], (cap, got)
     assert {"mid", "contract"} <= routes
+
+
+@pytest.mark.parametrize("form,cap,d", [
+    ("fp32", 8, 2), ("fp32", 64, 4), ("fp16f6", 100, 3), ("bf16x3", 300, 4),
+])
+def test_flagged_samples_are_counted_out_of_all(host, form, cap, d):
+    """The message of MPS_ENUMERIC names the samples of every chain of the
+    call, whatever kernels the chains take."""
+    dl = [d] * 9
+    chi = synth.ramp_bonds(dl, cap)
+    h, _ = _handle(form)
+    host.host_set_flagged(7)
+    assert _sample(h, chi, dl, 400) == mps.MPS_ENUMERIC
+    assert mps.mps_last_error().startswith("7 of 400 samples"), mps.mps_last_error()
+    assert _batch(h, [(chi, dl), ([1, 2, 1], [2, 2]), (chi, dl)], 50) == mps.MPS_ENUMERIC
+    assert mps.mps_last_error().startswith("7 of 150 samples"), mps.mps_last_error()
+    mps.mps_destroy(h)
