@@ -249,6 +249,8 @@ constexpr size_t kMidPackedBytes = size_t(1) << 30;
 // 0.97 to 1.09 at 48000 and 0.95 to 1.05 at 65536, where the per-site tiles
 // fill the chip.
 constexpr int64_t kMidRowsF32 = 40960;
+// Workgroups of one launch: HIP takes fewer than 2^32 threads in a dimension.
+constexpr int64_t grid_items(int threads) { return (int64_t)0xFFFFFFFFll / threads; }
 
 // Whether every site of a chain fits the persistent medium-bond kernel.
 bool mid_eligible(const Chain& c, int precision) {
@@ -568,6 +570,9 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   int64_t nc = o.n_chunk > 0 ? o.n_chunk : kDefaultChunk;
   nc = std::min<int64_t>(nc, N);
   nc = std::min<int64_t>(nc, (int64_t)1 << 30);
+  // one small-bond launch per chunk: 2^28 samples over its chains (the
+  // outcomes do not depend on the chunk)
+  if (nsmall) nc = std::min<int64_t>(nc, grid_items(mps::kSmallThreads) / nsmall * mps::kSmallRows);
   auto nstate_for = [&](int64_t rows) -> int64_t { return site_outer ? (N + rows - 1) / rows : 1; };
   // problem tables: one set per left-vector state, plus the chunk arguments
   auto table_for = [&](int64_t nstate) -> size_t {
@@ -624,7 +629,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
       mid_data += mid_bytes(c, o.precision);
       tables += mid_table_bytes(c);
     }
-    fits = fits && packed <= kMidPackedBytes;
+    fits = fits && packed <= kMidPackedBytes &&
+           (int64_t)chains.size() * ((nc + mps::kMidRows - 1) / mps::kMidRows) <= grid_items(mps::kMidThreads);
     // the plan with the chains on this path, given up if it is over the cap
     const int B0 = B, M0 = Mmax;
     mids.swap(chains);

@@ -192,6 +192,7 @@ struct InitProb {
 // d_k <= kSmallD at every site go through all their sites in one launch, 16
 // samples per workgroup (an "item"), left vectors and W kept in LDS.
 constexpr int kSmallRows = 16;
+constexpr int kSmallThreads = 256;  // of a workgroup
 constexpr int kSmallChi = 32;
 constexpr int kSmallD = 4;
 
@@ -217,6 +218,7 @@ hipError_t launch_sweep_small(const SmallChain* chains, const int* item_start, i
 // have at most kMidGroups groups of 64 complex columns (d * ceil(chi_r / 64))
 // and bonds <= kMidChi, 32 samples per workgroup.
 constexpr int kMidRows = 32;
+constexpr int kMidThreads = 512;  // of the largest workgroup
 constexpr int kMidGroups = 16;
 constexpr int kMidChi = 256;
 constexpr int kMidUnits = 8;  // FP32: units of 32 complex columns of a site (two per group)

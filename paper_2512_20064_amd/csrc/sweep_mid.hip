@@ -82,6 +82,7 @@ template <int FORM, int NW, int GPW>
 __device__ inline void sweep_mid_body(const MidChain* chains, const int* item_start, int nchain, int slices, int sp,
                                       const ChunkArgs* chp, uint64_t seed, int* nflag) {
   constexpr int NTHR = 64 * NW;
+  static_assert(NTHR <= kMidThreads, "the host plans launches with the largest workgroup");
   constexpr int LPR = NTHR / R;  // lanes per row in the decision; sites per block
   constexpr bool F8F6 = FORM == kFp16F8 || FORM == kFp16F6;
   typedef MidOps<FORM> Ops;

@@ -38,7 +38,8 @@ constexpr int NTHR = 64 * NW;
 constexpr int LPR = NTHR / R;             // lanes per row in the decision; sites per block
 constexpr int LP = R + 1;                 // pitch of the left-vector planes
 constexpr int KU = 8;                     // K steps (complex l) per load unit
-static_assert(R == 32 && LPR == 16 && kMidUnits == NW && kBK == 2 * KU, "lane roles and accumulation blocks below");
+static_assert(R == 32 && LPR == 16 && NTHR == kMidThreads && kMidUnits == NW && kBK == 2 * KU,
+              "lane roles and accumulation blocks below");
 
 __device__ inline void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt at their maxima

@@ -49,7 +49,7 @@ constexpr int R = kSmallRows;   // samples per workgroup
 constexpr int CHI = kSmallChi;  // largest bond
 constexpr int DM = kSmallD;     // largest physical dimension
 constexpr int NC = CHI * DM;    // largest d * chi_r (complex columns of W)
-constexpr int NTHR = 256;
+constexpr int NTHR = kSmallThreads;
 constexpr int NG = NC / 16 / 4;  // column groups per wave
 constexpr int NQ = CHI / 4;      // register quads of 4 complex l
 constexpr int NSTEP = CHI / 2;   // K steps of 2 complex l

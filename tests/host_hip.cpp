@@ -166,6 +166,7 @@ hipError_t launch_measure(int, const MeasureProb*, int nprob, const ChunkArgs*, 
 }
 hipError_t launch_sweep_small(const SmallChain*, const int*, int nchain, int items, const ChunkArgs* ch, uint64_t, int*,
                               hipStream_t) {
+  if (nchain <= 0 || items <= 0) return hipSuccess;
   line("small nchain=%d items=%d rows=%d", nchain, items, ch->rows);
   return grid((unsigned)items, 256);
 }
@@ -177,6 +178,7 @@ hipError_t launch_sweep_mid(int, int groups, const MidChain*, const int*, int nc
 }
 hipError_t launch_sweep_mid_f32(const MidChain*, const int*, int nchain, int items, int, const ChunkArgs* ch, uint64_t,
                                 int*, hipStream_t) {
+  if (nchain <= 0 || items <= 0) return hipSuccess;
   line("mid nchain=%d items=%d rows=%d", nchain, items, ch->rows);
   return grid((unsigned)items, 512);
 }

@@ -192,3 +192,26 @@ def test_flagged_samples_are_counted_out_of_all(host, form, cap, d):
     assert _batch(h, [(chi, dl), ([1, 2, 1], [2, 2]), (chi, dl)], 50) == mps.MPS_ENUMERIC
     assert mps.mps_last_error().startswith("7 of 150 samples"), mps.mps_last_error()
     mps.mps_destroy(h)
+
+
+@pytest.mark.parametrize("form,d,chi,B,N,n_chunk", [
+    ("fp32", [2], [1, 1], 1, (1 << 28) + 5, 1 << 29),              # small-bond kernel: 16 samples a workgroup
+    ("fp32", [2, 2], [1, 2, 1], 5000, 65536, 0),
+    ("fp16f6", [2], [1, 1], 20000, 1 << 21, 1 << 21),              # more than 2^31 workgroups in one launch
+    ("bf16x3", [5, 1], [1, 5, 5], 1, (1 << 28) + 5, 1 << 29),      # medium-bond kernel, 8 waves
+    ("fp16f6", [3, 1], [1, 40, 40], 1, (1 << 29) + 5, 1 << 30),    # and 4
+])
+def test_large_launches_stay_within_the_grid(host, form, d, chi, B, N, n_chunk):
+    """Chunks whose persistent launch would have 2^32 threads or more (HIP
+    refuses those) are cut, or the chain takes the per-site launches."""
+    host.host_reset(1 << 46)
+    h, _ = _handle(form, n_chunk=n_chunk)
+    desc, keep = mps.make_chain(_sites(len(d)), chi, d, 0, 0x1000, None)
+    descs = (mps.mps_chain * B)(*[desc] * B)
+    rc = host.mps_sample_batch(h, B, descs, mps.MPS_C64, N, 0, ctypes.c_uint64(1))
+    assert rc == 0, mps.mps_last_error()
+    log = _log(host)
+    done = [f["rows"] for k, f in log if k in ("small", "mid")] or \
+        [f["rows"] for k, f in log if k == "measure"][::len(d)]
+    assert sum(done) == N
+    mps.mps_destroy(h)
