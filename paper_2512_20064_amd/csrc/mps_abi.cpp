@@ -602,6 +602,23 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
       return fail(MPS_ENOMEM, "scratch for %lld-sample chunks (%zu B) plus site staging (%zu B) exceeds "
                   "%s (%lld B)", (long long)nc, scratch_for(nc, nullptr), stage_need, cap_name, (long long)cap);
   }
+  // Device memory kept by the handle, grown on demand.
+  auto grow = [&](void*& ptr, size_t& have, size_t need, const char* what) -> int {
+    if (need <= have) return MPS_OK;
+    if (ptr) {
+      if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
+      (void)hipFree(ptr);
+      ptr = nullptr;
+      have = 0;
+    }
+    if ((e = hipMalloc(&ptr, need)) != hipSuccess) {
+      ptr = nullptr;
+      (void)hipGetLastError();
+      return fail(MPS_ENOMEM, "hipMalloc(%zu) for %s failed: %s", need, what, hipGetErrorString(e));
+    }
+    have = need;
+    return MPS_OK;
+  };
   // ---- the persistent medium-bond kernel ----
   // Split forms, and FP32 with few samples; device-resident complex64 sites,
   // no displacement, every site of every chain within the kernel's registers
@@ -616,7 +633,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   // against 11290 at 5000; 24 chains, 64 samples: 4490 against 2880).  The
   // chunk is planned as for the per-site launches, and a capped call takes
   // this path only if its tables and packed sites fit, so that what fits under
-  // a cap does not change.
+  // a cap does not change; nor does a call fail for lack of memory that the
+  // per-site launches, with one packed site at a time, can do without.
   std::vector<Chain> mids;
   size_t mid_data = 0;  // packed sites
   if ((split || !lowp) && o.fused_small == 0 && !any_staged && !(single && o.displace) && !chains.empty()) {
@@ -631,13 +649,25 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
     }
     fits = fits && packed <= kMidPackedBytes &&
            (int64_t)chains.size() * ((nc + mps::kMidRows - 1) / mps::kMidRows) <= grid_items(mps::kMidThreads);
-    // the plan with the chains on this path, given up if it is over the cap
+    // the plan with the chains on this path, given up if it is over the cap or
+    // cannot be allocated
     const int B0 = B, M0 = Mmax;
     mids.swap(chains);
     B = 0;
     Mmax = 0;
     small_bytes += tables;
-    if (!fits || (cap > 0 && (int64_t)(scratch_for(nc, nullptr) + packed) > cap)) {
+    fits = fits && (cap == 0 || (int64_t)(scratch_for(nc, nullptr) + packed) <= cap);
+    const size_t need = scratch_for(nc, nullptr) + mid_data;
+    if (fits && !noalloc && need > h->scratch_bytes) {
+      // (asked first, so that a handle short of memory keeps its scratch)
+      size_t room = 0, all = 0;
+      fits = hipMemGetInfo(&room, &all) != hipSuccess || room + h->scratch_bytes >= need;
+      const int rg = fits ? grow(h->scratch, h->scratch_bytes, need, "sweep scratch") : (int)MPS_ENOMEM;
+      if (rg == MPS_OK) h->scratch_device = h->device;
+      else if (rg == MPS_ENOMEM) fits = false;
+      else return rg;
+    }
+    if (!fits) {
       mids.swap(chains);
       B = B0;
       Mmax = M0;
@@ -663,23 +693,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   const int64_t nstate = nstate_for(nc);
   const size_t table_bytes = table_for(nstate);
 
-  // ---- allocations (kept by the handle, grown on demand) ----
-  auto grow = [&](void*& ptr, size_t& have, size_t need, const char* what) -> int {
-    if (need <= have) return MPS_OK;
-    if (ptr) {
-      if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
-      (void)hipFree(ptr);
-      ptr = nullptr;
-      have = 0;
-    }
-    if ((e = hipMalloc(&ptr, need)) != hipSuccess) {
-      ptr = nullptr;
-      (void)hipGetLastError();
-      return fail(MPS_ENOMEM, "hipMalloc(%zu) for %s failed: %s", need, what, hipGetErrorString(e));
-    }
-    have = need;
-    return MPS_OK;
-  };
+  // ---- allocations ----
   int rc = MPS_OK;
   if (!noalloc) {
     if ((rc = grow(h->scratch, h->scratch_bytes, total, "sweep scratch"))) return rc;

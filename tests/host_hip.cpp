@@ -22,6 +22,7 @@ int g_flagged = 0;         // what the flag counter reads after a call
 const char* g_host_lo = nullptr;  // site pointers in [lo, hi) are pinned host memory
 const char* g_host_hi = nullptr;
 hipError_t g_err = hipSuccess;
+int g_mallocs = 0;
 int g_obj;  // address of every stream, event and graph
 
 hipError_t set(hipError_t e) { return g_err = e; }
@@ -60,10 +61,12 @@ void host_set_pinned(const char* lo, const char* hi) {
 }
 const char* host_log() { return g_log.c_str(); }
 size_t host_peak() { return g_peak; }
+int host_mallocs() { return g_mallocs; }
 
 // ---- memory ----
 hipError_t hipMalloc(void** p, size_t n) {
   if (g_now + n > g_limit) return set(hipErrorOutOfMemory);
+  ++g_mallocs;
   void* q = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (q == MAP_FAILED) return set(hipErrorOutOfMemory);
   g_live[(char*)q] = n;
@@ -80,6 +83,7 @@ hipError_t hipFree(void* p) {
   g_live.erase(it);
   return hipSuccess;
 }
+hipError_t hipMemGetInfo(size_t* room, size_t* all) { return *all = g_limit, *room = g_limit - g_now, hipSuccess; }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind k, hipStream_t) {
   if (k == hipMemcpyDeviceToHost && n == sizeof(int)) std::memcpy(dst, &g_flagged, n);  // the flag counter
   else std::memcpy(dst, src, n);

@@ -215,3 +215,26 @@ def test_large_launches_stay_within_the_grid(host, form, d, chi, B, N, n_chunk):
         [f["rows"] for k, f in log if k == "measure"][::len(d)]
     assert sum(done) == N
     mps.mps_destroy(h)
+
+
+@pytest.mark.parametrize("form", ["bf16x3", "fp16f6"])
+def test_medium_bond_call_falls_back_when_memory_is_short(host, form):
+    """A call whose packed sites do not fit in the memory that is left takes
+    the per-site launches, which need one packed site at a time."""
+    d, chi = [4] * 400, synth.ramp_bonds([4] * 400, 128)
+    for limit, want in ((1 << 26, "contract"), (1 << 30, "mid"), (1 << 26, "contract")):
+        host.host_reset(limit)
+        h, _ = _handle(form)
+        n0 = host.host_mallocs()
+        for _ in range(3):
+            assert _sample(h, chi, d, 16) == 0, mps.mps_last_error()
+            assert {k for k, _ in _log(host)} & {"mid", "contract"} == {want}
+        assert host.host_mallocs() == n0 + 1  # the scratch is kept from call to call
+        host.host_reset(1 << 30)  # memory is free again: the same handle
+        assert _sample(h, chi, d, 16) == 0, mps.mps_last_error()
+        assert {k for k, _ in _log(host)} & {"mid", "contract"} == {"mid"}
+        mps.mps_destroy(h)
+    host.host_reset(1 << 20)  # too little for either
+    h, _ = _handle(form)
+    assert _sample(h, chi, d, 16) == mps.MPS_ENOMEM
+    mps.mps_destroy(h)
