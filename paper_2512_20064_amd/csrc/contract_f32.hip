@@ -90,16 +90,15 @@ __device__ inline void f32_epilogue(const ContractProb& a, const floatx16 (&tot)
 
   // Epilogue 2: partial weight of this (row, branch, 64-column tile).
   // Columns past chi_r were zero-filled, so they add nothing.  Reduction
-  // order is fixed (the two blocks of a lane, the lanes by xor butterfly,
-  // then the two wave columns of the tile), so the result depends neither on
-  // scheduling nor on the variant (both have the same two wave columns).
+  // order is fixed (the two blocks of a lane in one fused multiply-add, the
+  // lanes by xor butterfly, then the two wave columns of the tile), so the
+  // result depends neither on scheduling nor on the variant (both have the same
+  // two wave columns); sweep_mid_f32.hip adds in the same order.
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      float s = 0.f;
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) s += tot[rb][cb][v] * tot[rb][cb][v];
+      float s = __builtin_fmaf(tot[rb][0][v], tot[rb][0][v], tot[rb][1][v] * tot[rb][1][v]);
 #pragma unroll
       for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 32);
       if (j == 0) red[(wave & 1) * BM + wr + rb * 32 + (v >> 2) * 8 + half * 4 + (v & 3)] = s;
