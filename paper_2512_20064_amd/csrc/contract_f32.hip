@@ -262,23 +262,25 @@ __global__ __launch_bounds__(F32Tile<BM>::NTHR, 2) void contract_f32_kernel(cons
 // and no transposition: a lane reads two K values of its row, both
 // parts, as one 16-byte chunk and keeps its part.  The chunks of a row are
 // permuted by (row >> 1) & 7, so that the 16 rows of a read phase lie in
-// distinct banks.  Rows past the chunk, columns past chi_r and K past the
-// tensor are zeros by the descriptors' ranges, or meet zeros.
+// distinct banks.  Rows past the chunk, columns past chi_r and site-tensor rows
+// past K are zeros by the descriptors' ranges; K values past a left vector are
+// the next row's first ones and meet those zeros (they are finite: the
+// measurement writes zeros for a flagged sample).
 //
 // What bounds it: the FP32 matrix cores, 127 of the 137 TFLOP/s that a library
 // product reaches here.  Sweep of 18 sites, 16384 samples, chi = 1024: 36.8 ms
-// against 44.0 for the register-staged kernel below (35.4 without its loads and
+// against 44.0 for the register-staged kernel above (35.4 without its loads and
 // LDS stores, 39.0 without its second accumulation level); with three stages
 // and two workgroups per CU 38.7, and with the row blocks one after the other,
 // each joining the totals during the other's matrix instructions, 39.5.
-// Sites with odd bonds, or misaligned, take the kernel below.
+// Sites with odd bonds, or misaligned, take the kernel above.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int DBM = 128;
 constexpr int DST = 2;
 constexpr int DLB = DBM * BK * 8;          // bytes of a left-vector stage
 constexpr int DSTAGE = DLB + BK * BNC * 8;
 constexpr int DIPW = DSTAGE / 1024 / 4;    // 1 KiB load instructions per wave and stage
-static_assert(DIPW == 6, "waits below");
+static_assert(DST == 2 && DIPW == 6, "load roles and waits below");
 
 __global__ __launch_bounds__(256, 3) void contract_f32_direct(const ContractProb* probs, const int* tn_start,
                                                               int nprob, int tn_total, int tiles_m, int per_xcd,
@@ -349,15 +351,14 @@ __global__ __launch_bounds__(256, 3) void contract_f32_direct(const ContractProb
   const unsigned bcol = (unsigned)(DLB + (2 * wc + (j ^ half)) * 4);
   const unsigned sgn = (half && !(j & 1)) ? 0x80000000u : 0u;
   const int nkt = (a.K + BK - 1) / BK;
-  int issued = 0;
-  issue(issued++);
+  issue(0);
   for (int kt = 0; kt < nkt; ++kt) {
-    // Stage kt landed (stage kt + 1 may stay in flight) and this wave's LDS
-    // reads of stage kt - 1 are done; after the barrier its buffer is refilled.
-    if (issued > kt + 1) __builtin_amdgcn_s_waitcnt(0x0070 | DIPW);  // vmcnt(DIPW) lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);                         // vmcnt(0) lgkmcnt(0)
+    // Stage kt landed and this wave's LDS reads of stage kt - 1 are done; after
+    // the barrier its buffer takes stage kt + 1, which arrives during the matrix
+    // instructions of stage kt.
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     asm volatile("s_barrier" ::: "memory");
-    if (issued < nkt) issue(issued++);
+    if (kt + 1 < nkt) issue(kt + 1);
     const char* st = lds + (kt % DST) * DSTAGE;
 #pragma unroll
     for (int q = 0; q < BK / 2; ++q) {
