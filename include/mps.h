@@ -366,8 +366,10 @@ typedef struct {
 /*
  * Tile autotuner (Section 3.4.2: site-varying bond dimensions, so each site
  * shape gets its own choice).  For every distinct site shape of the chains
- * that take per-site launches (chains handled by the persistent small-bond
- * kernel are skipped), in the handle's precision form: the site tensor is
+ * (those of the persistent small-bond kernel are skipped; the persistent
+ * medium-bond kernels have no tiles, but their chains take the per-site
+ * launches too, for instance in a batch with larger ones, and are timed), in
+ * the handle's precision form: the site tensor is
  * packed with each tile's padding and one contraction launch of `rows`
  * samples is timed per tile (one warm-up, three timed; operand noise of the
  * sweep's magnitudes in the left vectors).  The narrow tile is chosen when it

@@ -661,7 +661,8 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
     if (fits && !noalloc && need > h->scratch_bytes) {
       // (asked first, so that a handle short of memory keeps its scratch)
       size_t room = 0, all = 0;
-      fits = hipMemGetInfo(&room, &all) != hipSuccess || room + h->scratch_bytes >= need;
+      if ((e = hipMemGetInfo(&room, &all)) != hipSuccess) return hip_fail(e, "hipMemGetInfo");
+      fits = room + h->scratch_bytes >= need;
       const int rg = fits ? grow(h->scratch, h->scratch_bytes, need, "sweep scratch") : (int)MPS_ENOMEM;
       if (rg == MPS_OK) h->scratch_device = h->device;
       else if (rg == MPS_ENOMEM) fits = false;
@@ -841,7 +842,7 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   for (int64_t c = 0; c < nchunks; ++c)
     cargs[c] = mps::ChunkArgs{(int)std::min<int64_t>(nc, N - c * nc), 0, c * nc, n_offset};
   const size_t chunk_off = site_outer ? tab.put(cargs) : tab.put(std::vector<mps::ChunkArgs>(1, cargs[0]));
-  // small-bond chains: site pointers, bonds and dimensions in the tables, 32
+  // small-bond chains: site pointers, bonds and dimensions in the tables, 16
   // samples per workgroup
   size_t small_off = 0, small_start_off = 0;
   int small_items = 0;
@@ -1549,8 +1550,10 @@ int mps_autotune_tiles(mps_handle h, int32_t B, const mps_chain* chains_in, int6
   const mps_options& o = h->opt;
   const bool lowp = o.precision != MPS_FP32;
   const int form = lowp ? lp_form(o.precision) : 0;
-  // distinct shapes of the chains that take per-site launches, each with one
-  // of its site tensors (packed for the timing launches)
+  // distinct shapes of the chains, each with one of its site tensors (packed
+  // for the timing launches).  Small-bond chains never take the per-site
+  // launches; medium-bond chains do in batches with larger chains, displaced,
+  // or in FP32 with many samples, so theirs are timed.
   std::map<std::array<int, 3>, const void*> shapes;
   Shape all;
   for (int b = 0; b < B; ++b) {

@@ -87,7 +87,7 @@ __device__ inline void sweep_mid_body(const MidChain* chains, const int* item_st
   constexpr bool F8F6 = FORM == kFp16F8 || FORM == kFp16F6;
   typedef MidOps<FORM> Ops;
   constexpr int UK = Ops::UK;
-  // units in flight: with one W group a wave has registers for 6 slices
+  // units in flight: 4 slices with one W group per wave (6 spill), else 2
   constexpr int DEPTH = (GPW == 1 ? 4 : 2) / UK;
   __shared__ float qp[R][NGMAX];
   __shared__ __attribute__((aligned(16))) double qd[R][LPR];

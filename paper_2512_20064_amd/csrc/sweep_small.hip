@@ -4,9 +4,9 @@
 // samples, over chains, and over the sites of Section 2.2's sequential
 // workflow without returning to memory between sites).
 //
-// Eligible chains have chi_k <= 32 and d_k <= 4 at every site (larger bonds
-// run faster in the grouped per-site launches, which tile the contraction
-// over many more samples at once).  Per site the workgroup
+// Eligible chains have chi_k <= 32 and d_k <= 4 at every site: W of 16 samples
+// then fits the LDS and registers of three workgroups per CU.  Per site the
+// workgroup
 //   1. contracts the site tensor with the 16 left vectors on
 //      v_mfma_f32_16x16x4f32: W is 16 x (d * chi_r) complex, at most 8 groups
 //      of 16 complex columns, two per wave.  A wave loads the columns that it
