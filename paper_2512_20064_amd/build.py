@@ -49,5 +49,19 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_checks(verbose: bool = False) -> str:
+    """Compile the device checks of the tests (tests/e2m3_device.hip) to
+    tests/libe2m3_device.so; returns its path."""
+    tests = os.path.join(ROOT, "tests")
+    lib = os.path.join(tests, "libe2m3_device.so")
+    cmd = [hipcc(), *HIP_FLAGS, "-x", "hip", "-I", CSRC, "-shared", os.path.join(tests, "e2m3_device.hip"),
+           "-o", lib + ".tmp"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(lib + ".tmp", lib)
+    return lib
+
+
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))
