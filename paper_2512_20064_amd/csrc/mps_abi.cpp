@@ -659,10 +659,11 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
     fits = fits && (cap == 0 || (int64_t)(scratch_for(nc, nullptr) + packed) <= cap);
     const size_t need = scratch_for(nc, nullptr) + mid_data;
     if (fits && !noalloc && need > h->scratch_bytes) {
-      // (asked first, so that a handle short of memory keeps its scratch)
-      size_t room = 0, all = 0;
-      if ((e = hipMemGetInfo(&room, &all)) != hipSuccess) return hip_fail(e, "hipMemGetInfo");
-      fits = room + h->scratch_bytes >= need;
+      if (h->scratch_bytes > 0) {  // asked first, so that a handle short of memory keeps its scratch
+        size_t room = 0, all = 0;
+        if ((e = hipMemGetInfo(&room, &all)) != hipSuccess) return hip_fail(e, "hipMemGetInfo");
+        fits = room + h->scratch_bytes >= need;
+      }
       const int rg = fits ? grow(h->scratch, h->scratch_bytes, need, "sweep scratch") : (int)MPS_ENOMEM;
       if (rg == MPS_OK) h->scratch_device = h->device;
       else if (rg == MPS_ENOMEM) fits = false;
