@@ -242,6 +242,10 @@ struct Tables {
 };
 
 // Medium-bond chains (sweep_mid.hip): largest packed size of a call's chains.
+// It bounds what a handle keeps on the device beside the site tensors; it is no
+// line between two speeds (one chain of 600 sites, chi = 256, d = 4, 1.2 GiB
+// packed, fp16f6: 23.7 ms against 33.2 per site at 1000 samples, 90.8 against
+// 108.0 at 32768, had it been let through).
 constexpr size_t kMidPackedBytes = size_t(1) << 30;
 // FP32: most samples, over all chains, that take it.  Against the
 // per-site launches (chi 48 .. 128, up to 8 units, 14 sites): 1.8 to 2.8 times
@@ -542,9 +546,13 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   // no displacement: the whole chain goes through all its sites in one
   // launch per chunk (sweep_small.hip), with the FP32 contraction in every
   // precision form (at these bonds it is faster than the per-site 16-bit
-  // launches, and at least as accurate).  The other chains take the per-site
-  // launches below.  The choice depends on the chain alone, so a chain gives
-  // the same bits in a batch as in a call of its own.
+  // launches, and at least as accurate).  The medium-bond kernels take 1.2 to
+  // 1.9 times as long at 4096 samples; in the split forms they would be the
+  // faster ones from about 16384 samples on at chi >= 24, d = 4 (32 sites,
+  // chi = 32, 65536 samples: 1001 us here, 780 in fp16f6, 717 in bf16x3), but
+  // those calls would lose the FP32 contraction.  The other chains go on
+  // below.  The choice depends on the chain alone, so a chain gives the same
+  // bits in a batch as in a call of its own.
   std::vector<Chain> smalls;
   if (o.fused_small == 0 && !any_staged && !(single && o.displace)) {
     std::vector<Chain> bigs;
@@ -630,8 +638,10 @@ int run_sweep(mps_ctx* h, std::vector<Chain> chains, int64_t N, int64_t n_offset
   // and carry the others along (6 and 24 chains, 20 to 40 sites, chi <= 400,
   // fp16f6, the chains that fit taken out of the launches: 3470 us against
   // 2630 and 5300 against 5250 at 1500 samples, 4770 against 4450 and 10770
-  // against 11290 at 5000; 24 chains, 64 samples: 4490 against 2880).  The
-  // chunk is planned as for the per-site launches, and a capped call takes
+  // against 11290 at 5000; 24 chains, 64 samples: 4490 against 2880).  There
+  // is no condition on the samples: at 100000 the chains taken out would gain 5
+  // to 10 %.
+  // The chunk is planned as for the per-site launches, and a capped call takes
   // this path only if its tables and packed sites fit, so that what fits under
   // a cap does not change; nor does a call fail for lack of memory that the
   // per-site launches, with one packed site at a time, can do without.

@@ -29,10 +29,10 @@
 // (3500 the matrix instructions, 2050 at their peak rate; 1700 the loads of
 // the next site, 32 KiB per CU from L2; 2100 the measurement) when the samples
 // are few, the FP32 matrix cores when the chip is full.  M = 32, d = 4,
-// chi = 32, N = 4096: 174 us a call, against 500 us for 32-sample workgroups
-// that staged the site tensor through LDS and kept every step of a sample's
-// decision in line.  Spreading the loads over the measurement and placing the
-// swaps between the matrix instructions by hand changed nothing (180 us).
+// chi = 32, N = 4096: 163 us a call (the launch 116), against 497 us for
+// 32-sample workgroups that staged the site tensor through LDS and kept every
+// step of a sample's decision in line.  Spreading the loads over the measurement
+// and placing the swaps between the matrix instructions by hand changed nothing.
 
 #include "philox.h"
 #include "sweep.h"
