@@ -245,3 +245,25 @@ def test_small_bond_launch_of_more_than_2_28_samples():
         s.close()
     assert torch.equal(got[0], got[1])
     assert abs(got[0].float().mean().item() - 0.64) < 1e-3
+
+
+@pytest.mark.parametrize("form,d,cap", [("fp32", 4, 32), ("fp32", 3, 27), ("fp32", 2, 16), ("fp32", 2, 100),
+                                        ("fp32", 3, 45), ("fp16f6", 4, 100), ("bf16x3", 3, 65)])
+def test_site_tensors_eight_bytes_off(form, d, cap):
+    """Site tensors that start and end in the middle of 16 bytes: the bits of
+    aligned ones."""
+    from paper_2512_20064_amd import mps
+    from tests.parity_util import upload
+    print(f"[gpu-case] sites 8 bytes off {form} d={d} cap={cap}", flush=True)
+    dev = upload(_chain(7, [d] * 9, cap))
+    off = []
+    for x in dev:
+        buf = torch.full((x.numel() + 2,), float("nan"), dtype=torch.complex64, device="cuda")
+        buf[1:-1] = x.reshape(-1)
+        off.append(buf[1:-1].view(x.shape))
+    assert all(x.data_ptr() % 16 == 8 for x in off)
+    s = mps.Sampler(0, precision=form)
+    a, b = s.sample(dev, 77, 5, emit_n=77), s.sample(off, 77, 5, emit_n=77)
+    torch.cuda.synchronize()
+    _same(a, b)
+    s.close()
